@@ -135,7 +135,10 @@ Params make_params(const sdtw_desc *d, const Layout &L, const float *x, const fl
     p.spin_limit = g_spin_limit;
     p.x = x; p.y = y;
     p.hdr = reinterpret_cast<Header *>(base + L.off_hdr);
-    p.rfinal = reinterpret_cast<double *>(base + L.off_rfinal);
+    p.c2f = (float)p.c2d;
+    p.rfinal = reinterpret_cast<uint64_t *>(base + L.off_rfinal);
+    p.cmax = reinterpret_cast<float2 *>(base + L.off_cmax);
+    p.nslots = 0;  // (set by the forward call)
     p.xn = reinterpret_cast<float *>(base + L.off_xn);
     p.yn = reinterpret_cast<float *>(base + L.off_yn);
     p.Dp = L.Dp;
@@ -147,10 +150,10 @@ Params make_params(const sdtw_desc *d, const Layout &L, const float *x, const fl
     p.yh_stride = d->y_batch_stride == 0 ? 0 : (int64_t)d->M * L.Dp * 2;
     p.brow = reinterpret_cast<unsigned long long *>(base + L.off_brow);
     p.brow_b = reinterpret_cast<unsigned long long *>(base + L.off_brow_b);
-    p.R = reinterpret_cast<double *>(base + L.off_R);
-    p.Q = reinterpret_cast<double *>(base + L.off_Q);
+    p.R = reinterpret_cast<uint64_t *>(base + L.off_R);
+    p.Q = reinterpret_cast<uint64_t *>(base + L.off_Q);
     p.two_sweep = L.two_sweep;
-    p.ckpt = reinterpret_cast<double *>(base + L.off_ckpt);
+    p.ckpt = reinterpret_cast<uint64_t *>(base + L.off_ckpt);
     p.cost = reinterpret_cast<float *>(base + L.off_cost);
     p.E = L.compact_E ? nullptr : reinterpret_cast<float *>(base + L.off_E);  // (compact: the caller's E_out, if any)
     p.nz = reinterpret_cast<unsigned char *>(base + L.off_nz);
@@ -268,7 +271,7 @@ unsigned prep_grid(const Params &p, int64_t norm_rows)
     const size_t fill = ((size_t)p.B * p.nbands * p.M + 255) / 256;
     const size_t rows = (size_t)(norm_rows + 15) / 16;
     const size_t g = fill > rows ? fill : rows;
-    return (unsigned)(g < 1 ? 1 : (g > 8192 ? 8192 : g));
+    return (unsigned)(g < 1 ? 1 : (g > kMaxSlots ? kMaxSlots : g));
 }
 
 int forward_impl(const sdtw_desc *d, const float *x, const float *y, float *value, void *ws, hipStream_t st,
@@ -276,7 +279,7 @@ int forward_impl(const sdtw_desc *d, const float *x, const float *y, float *valu
 {
     (void)hipGetLastError();  // what an earlier, unrelated call left behind is not this call's error
     const Layout L = layout_of(d);
-    const Params p = make_params(d, L, x, y, ws, x_len, y_len, pieces);
+    Params p = make_params(d, L, x, y, ws, x_len, y_len, pieces);
     // Unfused mode, small problems: the start of the call is folded into the cost-tensor kernel (one
     // launch instead of two).  Not with a band constraint or length vectors (tiles outside them are
     // skipped), not without 16-byte rows, and only where the tiles are few (fewer than 512 of 128 x 128):
@@ -287,13 +290,15 @@ int forward_impl(const sdtw_desc *d, const float *x, const float *y, float *valu
                         tiles128 < 512;
     if (!folded) {
         ProfScope ps("forward_prep", st);
-        forward_prep_kernel<<<prep_grid(p, L.xn_count + L.yn_count), 256, 0, st>>>(p, L.xn_count, L.yn_count);
+        p.nslots = (int)prep_grid(p, L.xn_count + L.yn_count);
+        forward_prep_kernel<<<p.nslots, 256, 0, st>>>(p, L.xn_count, L.yn_count);
     }
     if (d->mode == SDTW_UNFUSED) {
         ProfScope ps("cost_tensor", st);
         // 128 x 128 tiles, or 128 x 64 when those would leave most of the chip idle
         const bool narrow = tiles128 < 512;
         dim3 gh(narrow ? (d->M + 63) / 64 : (d->M + 127) / 128, (d->N + 127) / 128, d->B);
+        if (folded) p.nslots = (int)(gh.x * gh.y * gh.z);  // fewer than 2 * 512 tiles
         auto launch = [&](auto kg) {
             constexpr int KG = decltype(kg)::value;
             if (folded)
