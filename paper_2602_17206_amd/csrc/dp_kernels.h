@@ -60,6 +60,18 @@ constexpr int kHandDoubles = kHandRing + kBandRows + kBlk;
 // state at the start of every macro-step (1/16 of R) and the backward recomputes each macro-step of
 // R before it uses it - from the cost block that is in the ring anyway, in either mode.
 constexpr bool dp_recompute(int /*kch*/, int slots) { return slots == 4; }
+// Shapes whose sweeps may use scaled table entries (Cell, device_core.h).  The scaled chain is shorter but gives a
+// SIMD as much to issue, so it pays where a consumer has a SIMD to itself and waits for its own results; in
+// the 4-band workgroups, whose consumer shares its SIMD with the producers, it does not (B = 32, L = 8192: 11.0 ms
+// logarithmic, 11.3 ms scaled), nor where the producer is what a macro-step waits for (D > 128: 670 against
+// 682 us at B = 16, L = 512, D = 200).
+constexpr bool may_scale(int kch, int slots) { return slots != 4 && kch != 0; }
+// In those shapes a producer fetches the band's incoming edge values (Courier) and the consumer, whose chain
+// everything waits for, issues no load; elsewhere the producers are the ones that are waited for and the consumer
+// fetches (B = 32, L = 8192: 11.3 ms against 14.0 ms).
+constexpr bool consumer_fetches(int kch, int slots) { return !may_scale(kch, slots); }
+// step of a macro-step at which such a consumer asks for the next one's values
+constexpr int kPeekStep = 24;
 constexpr float kBigCost = 3.0e38f;  // cost of a cell outside the grid
 constexpr int kStatusTimeoutDp = 6;  // SDTW_ERR_TIMEOUT
 
@@ -151,6 +163,7 @@ constexpr bool renorm_after(int u) { return (u & 15) >= 14; }
 template <int THREADS> __device__ __forceinline__ void find_cost_maximum(const Params &p, float2 *wave_max)
 {
     float2 mx = make_float2(0.f, 0.f);
+#pragma unroll 4
     for (int i = threadIdx.x; i < p.nslots; i += THREADS) {
         const float2 v = p.cmax[i];
         mx.x = fmaxf(mx.x, v.x);
@@ -168,7 +181,7 @@ template <int THREADS> __device__ __forceinline__ bool use_scaled(const Params &
         mx.x = fmaxf(mx.x, wave_max[i].x);
         mx.y = fmaxf(mx.y, wave_max[i].y);
     }
-    return __builtin_amdgcn_readfirstlane((int)scaled_fits(p, mx)) != 0;
+    return __builtin_amdgcn_readfirstlane((int)(p.nslots > 0 && scaled_fits(p, mx))) != 0;
 }
 
 __device__ __forceinline__ float comp4(const float4 &v, int c)
@@ -219,11 +232,10 @@ __device__ __forceinline__ void publish_boundary(unsigned long long *row, int j,
 }
 
 // ---------------------------------------------------------------------------------------------
-// Courier: a producer wavefront carries the band's edge values between memory and LDS, so that the consumer, whose
-// chain everything waits for, issues no load and never waits for memory (its table stores are in flight all the
-// time, and a load's wait would include them: the memory counter is in order).  Double-buffered
-// by the parity of the macro-step: while the consumer runs macro-step sg, the courier publishes what sg - DIR left
-// behind and fetches what sg + DIR needs.
+// Courier: the band's edge values between memory and LDS.  The consumer publishes what a macro-step left behind as
+// soon as it is through with it (left to a producer, which does it behind the barrier and at a lower priority, every hop
+// takes longer: 427 -> 449 us at B = 32, L = 1024).  What the coming macro-step needs is fetched, double-buffered by
+// the parity of the macro-step, by a producer where may_scale() holds and by the consumer elsewhere.
 //   forward (DIR = +1): in: the row above, lane l < 32 brings column 32*sg + l; out: the band's last row, lanes
 //     32 .. 63 publish columns 32*sg - 63 + (l - 32)
 //   reverse (DIR = -1): in: the row below, lane l >= 32 brings column 32*sg - 63 + (l - 32), which lane 63 meets
@@ -344,7 +356,7 @@ __device__ __forceinline__ void load_cost_block(float4 (&v)[4], const float *__r
 // cs: what the costs are multiplied by (Params::c2f for scaled tables, else 1); kBigCost stays the marker it is
 __device__ __forceinline__ void store_cost_block(float *ring, const float4 (&v)[4], int rb, int cb, int lane, float cs)
 {
-    auto cost = [&](int it, int e) { return fminf(comp4(v[it], e) * cs, kBigCost); };
+    auto cost = [&](int it, int e) { return cs == 1.0f ? comp4(v[it], e) : fminf(comp4(v[it], e) * cs, kBigCost); };
     const int c4 = (lane & 7) * 4;
     const int phase = (cb + rb) & 3;
     if (phase != 3) {  // no entry of the block wraps around the ring: constant offsets from the lane's base
@@ -829,7 +841,7 @@ __global__ __launch_bounds__(256) void cost_tensor_prep_kernel(Params p)
     }
     __syncthreads();
     // (rows of a tile's edge are repeated inside it: they change no maximum)
-    store_cost_maximum(p, blk, tid < 128 ? xtab[tid].x : 0.f, tid < 32 * CB ? ytab[tid].x : 0.f);
+    if (p.nslots > 0) store_cost_maximum(p, blk, tid < 128 ? xtab[tid].x : 0.f, tid < 32 * CB ? ytab[tid].x : 0.f);
     float xn_r[16], m2is_r[16];
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
@@ -855,11 +867,11 @@ template <int SLOTS> struct WgShared {
 };
 
 // Values the band's edge row (last row in the forward sweep, first in the reverse sweep) produced
-// in a macro-step, one per step, for the neighbouring band: 64-bit entries [SLOTS][kEdgeOut] in LDS, the
-// macro-steps alternating between the first two runs of 32.  Every lane writes its value each step; only the
-// edge lane's address points into those, the others write to slots of their own behind them.  (Kept as an
+// in a macro-step, one per step, for the neighbouring band: 64-bit entries [SLOTS][kEdgeOut] in LDS.  Every
+// lane writes its value each step; only the edge lane's address points into the first 32, the others
+// write to slots of their own behind them.  (Kept as an
 // object of its own, so that these stores are known not to touch the ring or the incoming boundary values.)
-constexpr int kEdgeOut = 2 * kBlk + kBandRows + kBlk;
+constexpr int kEdgeOut = kBlk + kBandRows + kBlk;
 
 // Groups the wavefronts that share a SIMD as consumer (0) and producers (1, 2) of one band slot.
 // If the wavefronts are not spread evenly over the SIMDs, falls back to wavefront w -> role w/4,
@@ -910,7 +922,7 @@ __device__ __forceinline__ void forward_dp_body(const Params &p, float *__restri
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 
     if (threadIdx.x == 0) ticket_s = atomicAdd(&p.hdr->fwd_ticket, 1u);
-    find_cost_maximum<kThreads>(p, sh.wave_max);
+    if constexpr (may_scale(KCH, SLOTS)) find_cost_maximum<kThreads>(p, sh.wave_max);
     for (int e = threadIdx.x; e < SLOTS * kRingFloats; e += kThreads) (&sh.ring[0][0])[e] = kBigCost;
     int producer, slot;  // producer: 0 = consumer, 1.. = producer number
     if constexpr (SLOTS == 4) {
@@ -949,7 +961,8 @@ __device__ __forceinline__ void forward_dp_body(const Params &p, float *__restri
         }
         rg = sweep_range(p, k * kBandRows, k * kBandRows, nl, ml);
     }
-    const bool scaled = use_scaled<kThreads>(p, sh.wave_max);
+    bool scaled = false;
+    if constexpr (may_scale(KCH, SLOTS)) scaled = use_scaled<kThreads>(p, sh.wave_max);
     if (threadIdx.x == 0 && ticket == 0) p.hdr->scaled = scaled ? 1 : 0;  // for the kernels that read the tables
     const float cs = scaled ? p.c2f : 1.0f;
     const bool live = (k < p.nbands) && (b < p.B) && rg.hi >= rg.lo;
@@ -981,42 +994,39 @@ __device__ __forceinline__ void forward_dp_body(const Params &p, float *__restri
 
     // chained pair: slot 0's last row reaches slot 1 through LDS (hand), and memory besides, where alignment_kernel
     // looks for the columns that can hold a non-zero E
-    const bool row_from_lds = SLOTS == 2 && slot == 1, row_to_lds = SLOTS == 2 && slot == 0;
+    const bool row_from_lds = SLOTS == 2 && slot == 1;
+    constexpr bool kGet = consumer_fetches(KCH, SLOTS);
 
-    if (producer) {
-        // ------------------------------------------------------------------ producer wavefront
-        Courier<+1> cour;
+    Courier<+1> cour;
+    {
         const int kc = live ? k : 0;
         cour.in = p.brow + ((size_t)bb * p.nbands + (kc > 0 ? kc - 1 : 0)) * M;
         cour.out = p.brow + ((size_t)bb * p.nbands + kc) * M;
         cour.has_in = live && k > 0 && !row_from_lds;
         cour.emit = live && k + 1 < p.nbands;
-        auto publish = [&](int sg) {
-            if (sg >= rg.lo && sg <= rg.hi)
-                cour.publish(p, row_to_lds ? hand + (sg & 3) * kBlk : edge_out[slot] + (sg & 1) * kBlk, sg, lane);
-        };
+    }
+    if (producer) {
+        // ------------------------------------------------------------------ producer wavefront
         // start(): what the first macro-step needs; work(sg, late): the blocks of macro-step sg.  courier: this wavefront
         // carries the edge values
         auto produce = [&](bool courier, auto &&start, auto &&work) {
             if (live) {
-                if (courier) {
+                if (!kGet && courier) {
                     (&sh.edge_in[slot][0][0])[lane] = kBigBits;
                     cour.peek(p, rg.lo, lane);
                 }
                 start();
-                if (courier) cour.deliver(p, sh.edge_in[slot][rg.lo & 1], rg.lo, lane);
+                if (!kGet && courier) cour.deliver(p, sh.edge_in[slot][kGet ? 0 : rg.lo & 1], rg.lo, lane);
             }
             __syncthreads();
             for (int it = 0; it < niter; ++it) {
                 const int sg = rg.lo + it - lag;
-                if (courier) publish(sg - 1);
-                if (live && sg >= rg.lo && sg <= rg.hi) {
-                    work(sg, [&] { if (courier) cour.peek(p, sg + 1, lane); });
-                    if (courier) cour.deliver(p, sh.edge_in[slot][(sg + 1) & 1], sg + 1, lane);
+                                if (live && sg >= rg.lo && sg <= rg.hi) {
+                    work(sg, [&] { if (!kGet && courier) cour.peek(p, sg + 1, lane); });
+                    if (!kGet && courier) cour.deliver(p, sh.edge_in[slot][kGet ? 0 : (sg + 1) & 1], sg + 1, lane);
                 }
                 __syncthreads();
             }
-            if (courier) publish(rg.lo + niter - 1 - lag);
         };
         if constexpr (KCH > 0 && NPROD == 2) {
             // producer 1 makes (lower rows, sg), producer 2 makes (upper rows, sg+1)
@@ -1102,6 +1112,11 @@ __device__ __forceinline__ void forward_dp_body(const Params &p, float *__restri
     uint64_t fin = 0;
     const float *my_ring = ring + lane * kRingStride;
     uint64_t *eo = edge_out[slot];
+    if (kGet && CH != 1 && live) {
+        (&sh.edge_in[slot][0][0])[lane] = kBigBits;
+        cour.peek(p, rg.lo, lane);
+        cour.deliver(p, sh.edge_in[slot][kGet ? 0 : rg.lo & 1], rg.lo, lane);
+    }
     __syncthreads();
 
     for (int it = 0; it < niter; ++it) {
@@ -1110,7 +1125,7 @@ __device__ __forceinline__ void forward_dp_body(const Params &p, float *__restri
             const float *rd = my_ring + (sg & 3) * kBlk;
             // The row above, column 32*sg + u at step u: from the incoming boundary values, or from
             // the hand-over ring, where the band above put column c at slot (c + 63) mod 128.
-            const uint64_t *top0 = sh.edge_in[slot][sg & 1], *top1 = top0 + 1;  // step 0, steps 1..31
+            const uint64_t *top0 = sh.edge_in[slot][kGet ? 0 : sg & 1], *top1 = top0 + 1;  // step 0, steps 1..31
             if constexpr (CH == 1) {
                 top0 = hand + ((sg + 1) & 3) * kBlk + (kBlk - 1);
                 top1 = hand + ((sg + 2) & 3) * kBlk;
@@ -1118,16 +1133,17 @@ __device__ __forceinline__ void forward_dp_body(const Params &p, float *__restri
             // The macro-step's 32 cost values and its row above, read in one batch: read one per step they sit
             // between the steps' LDS stores, which they may not overtake, and each costs the chain a wait.
             float dcv[kBlk];
-            uint64_t tv[kBlk];
+            constexpr bool kBatchTop = SC;  // (behind the longer logarithmic step a read per step costs nothing)
+            [[maybe_unused]] uint64_t tv[kBlk];
 #pragma unroll
             for (int u = 0; u < kBlk; ++u) {
                 dcv[u] = rd[u];
-                tv[u] = u == 0 ? top0[0] : top1[u - 1];
+                if (kBatchTop) tv[u] = u == 0 ? top0[0] : top1[u - 1];
             }
-            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (kBatchTop) __builtin_amdgcn_sched_barrier(0);
             // Where this macro-step's values go: lane 63's are the band's last row (column
             // 32*sg + u - 63 at step u), the other lanes write to slots of their own.
-            uint64_t *my_eo = eo + ((lane == kBandRows - 1) ? (sg & 1) * kBlk : 2 * kBlk + lane);
+            uint64_t *my_eo = eo + ((lane == kBandRows - 1) ? 0 : kBlk + lane);
             if constexpr (CH == 0) my_eo = hand + ((lane == kBandRows - 1) ? (sg & 3) * kBlk : kHandRing + lane);
             uint64_t *Rs = RECOMP ? nullptr : Rk + (size_t)sg * kBlk * kBandRows;
             if constexpr (RECOMP) {
@@ -1137,7 +1153,8 @@ __device__ __forceinline__ void forward_dp_body(const Params &p, float *__restri
             auto steps = [&](auto capture) {
 #pragma unroll
                 for (int u = 0; u < kBlk; ++u) {
-                    const Cell<SC> up = cell_shr1(left, tv[u]);  // R[i-1][j]; lane 0 takes the row above the band
+                    if (kGet && CH != 1 && u == kPeekStep) cour.peek(p, sg + 1, lane);
+                    const Cell<SC> up = cell_shr1(left, kBatchTop ? tv[u] : (u == 0 ? top0[0] : top1[u - 1]));  // R[i-1][j]; lane 0 takes the row above the band
                     Cell<SC> cur = dp_cell<SC>(diag, up, left, dcv[u], c2d);
                     if (renorm_after(u)) renorm(cur);
                     const uint64_t bits = pack(cur);
@@ -1153,6 +1170,10 @@ __device__ __forceinline__ void forward_dp_body(const Params &p, float *__restri
                 steps(std::true_type{});
             else
                 steps(std::false_type{});
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            // the band's last row, for the band below (also from a chained pair's upper band: alignment_kernel reads it)
+            cour.publish(p, CH == 0 ? hand + (sg & 3) * kBlk : eo, sg, lane);
+            if (kGet && CH != 1) cour.deliver(p, sh.edge_in[slot][kGet ? 0 : (sg + 1) & 1], sg + 1, lane);
         }
         __syncthreads();
     }
@@ -1175,10 +1196,13 @@ __device__ __forceinline__ void forward_dp_body(const Params &p, float *__restri
             consume(std::integral_constant<int, -1>{}, scaled_c);
         }
     };
-    if (scaled)
-        consume_as(std::true_type{});
-    else
-        consume_as(std::false_type{});
+    if constexpr (may_scale(KCH, SLOTS)) {
+        if (scaled) {
+            consume_as(std::true_type{});
+            return;
+        }
+    }
+    consume_as(std::false_type{});
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1509,7 +1533,7 @@ __device__ __forceinline__ void reverse_dp_body(const Params &p, WgShared<SLOTS>
     }
 
     if (threadIdx.x == 0) ticket_s = atomicAdd(&p.hdr->bwd_ticket, 1u);
-    if constexpr (TSWEEP) find_cost_maximum<kThreads>(p, sh.wave_max);
+    if constexpr (may_scale(KCH, SLOTS)) find_cost_maximum<kThreads>(p, sh.wave_max);
     for (int e = threadIdx.x; e < SLOTS * kRingFloats; e += kThreads) (&sh.ring[0][0])[e] = kBigCost;
     int producer, slot;  // producer: 0 = consumer, 1.. = producer number
     if constexpr (SLOTS == 4) {
@@ -1548,11 +1572,8 @@ __device__ __forceinline__ void reverse_dp_body(const Params &p, WgShared<SLOTS>
         rg = sweep_range(p, (p.nbands - 1 - kk) * kBandRows, (p.nbands - 1 - kk) * kBandRows, nl, ml);
     }
     const int k = p.nbands - 1 - kk;
-    bool scaled;
-    if constexpr (TSWEEP)
-        scaled = use_scaled<kThreads>(p, sh.wave_max);
-    else
-        scaled = __builtin_amdgcn_readfirstlane(p.hdr->scaled) != 0;  // as the forward call had it
+    bool scaled = false;
+    if constexpr (may_scale(KCH, SLOTS)) scaled = use_scaled<kThreads>(p, sh.wave_max);
     const float cs = scaled ? p.c2f : 1.0f;
     const bool live = (kk < p.nbands) && (b < p.B) && rg.hi >= rg.lo;
     const int lag = (SLOTS == 2) ? kChainLag * slot : 0;
@@ -1592,19 +1613,18 @@ __device__ __forceinline__ void reverse_dp_body(const Params &p, WgShared<SLOTS>
     constexpr bool kProducerFlush = !GRAD && !TSWEEP && !(dp_recompute(KCH, SLOTS) && KCH > 4);
 
     // chained pair (slot 0: the lower band): its first row reaches slot 1 through LDS, and memory besides
-    const bool row_from_lds = SLOTS == 2 && slot == 1, row_to_lds = SLOTS == 2 && slot == 0;
+    const bool row_from_lds = SLOTS == 2 && slot == 1;
+    constexpr bool kGet = consumer_fetches(KCH, SLOTS);
 
-    if (producer) {
-        Courier<-1> cour;
+    Courier<-1> cour;
+    {
         const int kc = live ? k : 0;
         cour.has_in = live && k + 1 < p.nbands && !row_from_lds;
         cour.emit = live && k > 0;
         cour.in = p.brow_b + ((size_t)bb * p.nbands + (cour.has_in ? kc + 1 : kc)) * M;
         cour.out = p.brow_b + ((size_t)bb * p.nbands + kc) * M;
-        auto publish = [&](int sg) {
-            if (sg >= rg.lo && sg <= sg0)
-                cour.publish(p, row_to_lds ? hand + (sg & 3) * kBlk : edge_out[slot] + (sg & 1) * kBlk, sg, lane);
-        };
+    }
+    if (producer) {
         // Besides the cost blocks, the producers write out the E blocks the consumer finished in the
         // previous macro-step `done`: (upper rows, done) and (lower rows, done-1).  Each producer
         // touches only the rows it owns and flushes before it overwrites the same ring phase.
@@ -1618,25 +1638,23 @@ __device__ __forceinline__ void reverse_dp_body(const Params &p, WgShared<SLOTS>
         // (as in the forward sweep; upper, lower: the block rows whose finished E blocks this wavefront writes out)
         auto produce = [&](bool courier, bool upper, bool lower, auto &&start, auto &&work) {
             if (live) {
-                if (courier) {
+                if (!kGet && courier) {
                     (&sh.edge_in[slot][0][0])[lane] = kBigBits;
                     cour.peek(p, sg0, lane);
                 }
                 start();
-                if (courier) cour.deliver(p, sh.edge_in[slot][sg0 & 1], sg0, lane);
+                if (!kGet && courier) cour.deliver(p, sh.edge_in[slot][kGet ? 0 : sg0 & 1], sg0, lane);
             }
             __syncthreads();
             for (int it = 0; it < niter; ++it) {
                 const int sg = sg0 - (it - lag);
-                if (courier) publish(sg + 1);
-                if (live && sg >= rg.lo && sg <= sg0) {
+                                if (live && sg >= rg.lo && sg <= sg0) {
                     if (sg < sg0) flush(sg + 1, upper, lower);
-                    work(sg, [&] { if (courier) cour.peek(p, sg - 1, lane); });
-                    if (courier) cour.deliver(p, sh.edge_in[slot][(sg - 1) & 1], sg - 1, lane);
+                    work(sg, [&] { if (!kGet && courier) cour.peek(p, sg - 1, lane); });
+                    if (!kGet && courier) cour.deliver(p, sh.edge_in[slot][kGet ? 0 : (sg - 1) & 1], sg - 1, lane);
                 }
                 __syncthreads();
             }
-            if (courier) publish(sg0 - (niter - 1 - lag));
             if (live) flush(rg.lo, upper, lower);
         };
         // blocks the first macro-step reads: (upper rows, sg0-1), (lower rows, sg0-1), (lower rows, sg0-2)
@@ -1762,6 +1780,11 @@ __device__ __forceinline__ void reverse_dp_body(const Params &p, WgShared<SLOTS>
             if (k > 0 && lane < kBlk && jf < M) ftop_next = ftop_g[jf];
         }
     }
+    if (kGet && CH != 1 && live) {
+        (&sh.edge_in[slot][0][0])[lane] = kBigBits;
+        cour.peek(p, sg0, lane);
+        cour.deliver(p, sh.edge_in[slot][kGet ? 0 : sg0 & 1], sg0, lane);
+    }
 
     __syncthreads();
 
@@ -1771,14 +1794,14 @@ __device__ __forceinline__ void reverse_dp_body(const Params &p, WgShared<SLOTS>
             float *rd = my_ring + (sg & 3) * kBlk;
             // The row below, column 32*sg + u - 63 at step u: from the incoming boundary values, or
             // from the hand-over ring, where the band below put column c at slot c mod 128.
-            const uint64_t *bot = sh.edge_in[slot][sg & 1];
+            const uint64_t *bot = sh.edge_in[slot][kGet ? 0 : sg & 1];
             const uint64_t *bot31 = bot + (kBlk - 1), *bot0 = bot;  // step 31, steps 0..30
             if constexpr (CH == 1) {
                 bot31 = hand + ((sg - 1) & 3) * kBlk;
                 bot0 = hand + ((sg - 2) & 3) * kBlk + 1;
             }
             // lane 0's values are the band's first row (column 32*sg + u at step u)
-            uint64_t *my_eo = eo + ((lane == 0) ? (sg & 1) * kBlk : 2 * kBlk + lane);
+            uint64_t *my_eo = eo + ((lane == 0) ? 0 : kBlk + lane);
             if constexpr (CH == 0) my_eo = hand + ((lane == 0) ? (sg & 3) * kBlk : kHandRing + lane);
             uint64_t *Qs = TSWEEP ? Qk + (size_t)sg * kBlk * kBandRows : nullptr;
             const int sbase = sg * kBlk;
@@ -1844,15 +1867,16 @@ __device__ __forceinline__ void reverse_dp_body(const Params &p, WgShared<SLOTS>
 #pragma unroll
                 for (int u = kBlk - 1; u >= 0; --u) {
                     dcv[u] = rd[u];
-                    bv[u] = u == kBlk - 1 ? bot31[0] : bot0[u];
+                    if constexpr (SC) bv[u] = u == kBlk - 1 ? bot31[0] : bot0[u];
                 }
-                __builtin_amdgcn_sched_barrier(0);
+                if constexpr (SC) __builtin_amdgcn_sched_barrier(0);
             }
             auto steps = [&](auto corner, auto alive) {
 #pragma unroll
             for (int u = kBlk - 1; u >= 0; --u) {
+                if (kGet && CH != 1 && u == kBlk - 1 - kPeekStep) cour.peek(p, sg - 1, lane);
                 uint64_t below;
-                if constexpr (TSWEEP)
+                if constexpr (TSWEEP && SC)
                     below = bv[u];
                 else
                     below = u == kBlk - 1 ? bot31[0] : bot0[u];
@@ -1901,6 +1925,9 @@ __device__ __forceinline__ void reverse_dp_body(const Params &p, WgShared<SLOTS>
             else
                 steps(std::false_type{}, std::true_type{});
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            // the band's first row, for the band above
+            cour.publish(p, CH == 0 ? hand + (sg & 3) * kBlk : eo, sg, lane);
+            if (kGet && CH != 1) cour.deliver(p, sh.edge_in[slot][kGet ? 0 : (sg - 1) & 1], sg - 1, lane);
             // the E blocks this macro-step completed, (upper rows, sg) and (lower rows, sg-1): written
             // out by the producers during the next macro-step, or here
             // (both hold cells of this macro-step and the one before it only)
@@ -1934,10 +1961,13 @@ __device__ __forceinline__ void reverse_dp_body(const Params &p, WgShared<SLOTS>
             consume(std::integral_constant<int, -1>{}, scaled_c);
         }
     };
-    if (scaled)
-        consume_as(std::true_type{});
-    else
-        consume_as(std::false_type{});
+    if constexpr (may_scale(KCH, SLOTS)) {
+        if (scaled) {
+            consume_as(std::true_type{});
+            return;
+        }
+    }
+    consume_as(std::false_type{});
 }
 
 // ---------------------------------------------------------------------------------------------

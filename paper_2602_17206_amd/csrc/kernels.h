@@ -95,6 +95,7 @@ __global__ __launch_bounds__(256) void forward_prep_kernel(Params p, int64_t xro
         }
         return n;
     };
+    const bool want_max = p.nslots > 0;
     const int xl = longest(p.x_len, p.xn_stride, p.N), yl = longest(p.y_len, p.yn_stride, p.M);
     auto note_norm = [&](bool isx, int64_t lr, float norm) {
         const int32_t *lens = isx ? p.x_len : p.y_len;
@@ -168,7 +169,7 @@ __global__ __launch_bounds__(256) void forward_prep_kernel(Params p, int64_t xro
             }
             cur = nxt;
         }
-        store_cost_maximum(p, blockIdx.x, xmax, ymax);
+        if (want_max) store_cost_maximum(p, blockIdx.x, xmax, ymax);
         return;
     }
     // One wavefront per row, lanes stride over the features.  Up to 256 features stay in registers
@@ -243,7 +244,7 @@ __global__ __launch_bounds__(256) void forward_prep_kernel(Params p, int64_t xro
 #pragma unroll
         for (int c = 0; c < kRegs; ++c) cur[c] = nxt[c];
     }
-    store_cost_maximum(p, blockIdx.x, xmax, ymax);
+    if (want_max) store_cost_maximum(p, blockIdx.x, xmax, ymax);
 }
 
 // Does the workspace hold the forward of this descriptor?  Every field is read before any is

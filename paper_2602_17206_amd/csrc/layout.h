@@ -20,7 +20,7 @@ constexpr uint32_t kMagic = 0x53445457u;               // 'SDTW'
 // one as a (mantissa, scale) pair.
 constexpr uint64_t kBigBits = 0x7E37E43C00000000ull;
 constexpr double kBig = __builtin_bit_cast(double, kBigBits);
-constexpr int kMaxSlots = 8192;                        // workgroups of the kernel that makes the norms, at most
+constexpr int kMaxSlots = 1024;                        // workgroups that make the norms, at most, where the sweeps may use scaled entries
 constexpr int32_t kNoWindow = 0x3FFFFFFF;              // Params::window when there is no band constraint
 constexpr int kGuardBytes = 512;  // slack before/after regions that are read with clamped indices
 
@@ -183,7 +183,7 @@ struct Params {
     double c2d;             // log2(e)/gamma: paper units -> table units
     double inv_c2d;         // gamma*ln(2): table units -> paper units
     float c2f;              // c2d in float32: the scale of the costs in the (mantissa, scale) representation
-    int32_t nslots;         // entries of cmax
+    int32_t nslots;         // entries of cmax; 0: not wanted, logarithmic tables
     float2 *cmax;           // per workgroup of the kernel that makes the norms: largest ||x_i||^2 and ||y_j||^2 it saw
     int64_t x_stride, y_stride;    // batch strides of x, y (elements)
     int64_t xn_stride, yn_stride;  // batch strides of the norm vectors (0 when shared)

@@ -214,8 +214,9 @@ void launch_dp_kch(const sdtw_desc *d, const Layout &L, const Params &p, float *
                 const unsigned tasks = (unsigned)d->B * (unsigned)L.nbands;
                 // about four workgroups per compute unit: the wavefronts share SIMDs anyway, and one
                 // producer per band (two wavefronts per workgroup instead of three) leaves the consumers
-                // more of them (3 % at N = M = 1024, B = 32)
-                if (L.two_sweep && KCH > 0 && 2 * tasks > 900)
+                // more of them.  Not at D > 64: a single producer is what the (scaled) chain waits for then
+                // (N = M = 1024, B = 32, D = 128: 416 us, 337 us with two).
+                if (L.two_sweep && KCH > 0 && KCH < 8 && 2 * tasks > 900)
                     both_sweeps_kernel<KCH, 1, 1><<<2 * tasks, wg_threads(1, 1), 0, st>>>(p, value);
                 else if (L.two_sweep)
                     both_sweeps_kernel<KCH, 1, NP><<<2 * tasks, wg_threads(1, NP), 0, st>>>(p, value);
@@ -271,7 +272,7 @@ unsigned prep_grid(const Params &p, int64_t norm_rows)
     const size_t fill = ((size_t)p.B * p.nbands * p.M + 255) / 256;
     const size_t rows = (size_t)(norm_rows + 15) / 16;
     const size_t g = fill > rows ? fill : rows;
-    return (unsigned)(g < 1 ? 1 : (g > kMaxSlots ? kMaxSlots : g));
+    return (unsigned)(g < 1 ? 1 : (g > 8192 ? 8192 : g));
 }
 
 int forward_impl(const sdtw_desc *d, const float *x, const float *y, float *value, void *ws, hipStream_t st,
@@ -280,6 +281,8 @@ int forward_impl(const sdtw_desc *d, const float *x, const float *y, float *valu
     (void)hipGetLastError();  // what an earlier, unrelated call left behind is not this call's error
     const Layout L = layout_of(d);
     Params p = make_params(d, L, x, y, ws, x_len, y_len, pieces);
+    // Scaled table entries where the shape may use them (may_scale); the norms' maxima are wanted then.
+    const bool scaled = small_problem(d);
     // Unfused mode, small problems: the start of the call is folded into the cost-tensor kernel (one
     // launch instead of two).  Not with a band constraint or length vectors (tiles outside them are
     // skipped), not without 16-byte rows, and only where the tiles are few (fewer than 512 of 128 x 128):
@@ -290,15 +293,17 @@ int forward_impl(const sdtw_desc *d, const float *x, const float *y, float *valu
                         tiles128 < 512;
     if (!folded) {
         ProfScope ps("forward_prep", st);
-        p.nslots = (int)prep_grid(p, L.xn_count + L.yn_count);
-        forward_prep_kernel<<<p.nslots, 256, 0, st>>>(p, L.xn_count, L.yn_count);
+        unsigned grid = prep_grid(p, L.xn_count + L.yn_count);
+        if (scaled) p.nslots = (int)(grid = std::min(grid, (unsigned)kMaxSlots));  // every sweep workgroup reads them all:
+        // at B = 64, L = 512, D = 32 a step takes 180.3 us with at most 1024, 185.7 us with 2048
+        forward_prep_kernel<<<grid, 256, 0, st>>>(p, L.xn_count, L.yn_count);
     }
     if (d->mode == SDTW_UNFUSED) {
         ProfScope ps("cost_tensor", st);
         // 128 x 128 tiles, or 128 x 64 when those would leave most of the chip idle
         const bool narrow = tiles128 < 512;
         dim3 gh(narrow ? (d->M + 63) / 64 : (d->M + 127) / 128, (d->N + 127) / 128, d->B);
-        if (folded) p.nslots = (int)(gh.x * gh.y * gh.z);  // fewer than 2 * 512 tiles
+        if (folded && scaled) p.nslots = (int)(gh.x * gh.y * gh.z);  // fewer than kMaxSlots: at most twice tiles128 < 512
         auto launch = [&](auto kg) {
             constexpr int KG = decltype(kg)::value;
             if (folded)
