@@ -156,7 +156,7 @@ int sdtw_forward(const sdtw_desc *desc, const float *x, const float *y, float *v
  *     sdtw_workspace_status); a band that gives up waiting leaves NaN-free but meaningless values,
  *     as for sdtw_forward.
  */
-#define SDTW_STATIC_SCRATCH_BYTES (((size_t)64 << 20) + ((size_t)8 << 10)) /* 64 MiB, and the norms' maxima */
+#define SDTW_STATIC_SCRATCH_BYTES ((size_t)64 << 20)
 int sdtw_forward_static_scratch(const sdtw_desc *desc, const float *x, const float *y, float *value,
                                 void *stream);
 

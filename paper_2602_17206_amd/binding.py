@@ -265,7 +265,7 @@ def sdtw_forward_desc(desc, x, y, workspace, value, stream=None):
     return value
 
 
-STATIC_SCRATCH_BYTES = (64 << 20) + (8 << 10)
+STATIC_SCRATCH_BYTES = 64 << 20
 
 
 def sdtw_forward_static_scratch(desc, x, y, value, stream=None):

@@ -69,112 +69,12 @@ __device__ __forceinline__ double lane_shl1(double v, double fill)
     int hi = lane_shl1_i32(__double2hiint(v), __double2hiint(fill));
     return __hiloint2double(hi, lo);
 }
-// the same for the minimum of an int
-template <int CTRL, int ROW_MASK> __device__ __forceinline__ int dpp_min_i32_step(int v)
+// value of lane `src` (compile-time constant after unrolling) broadcast to the wavefront
+__device__ __forceinline__ double read_lane(double v, int src)
 {
-    return min(v, __builtin_amdgcn_update_dpp(v, v, CTRL, ROW_MASK, 0xf, false));
-}
-__device__ __forceinline__ int wave_min_i32(int v)
-{
-    v = dpp_min_i32_step<0x111, 0xf>(v);
-    v = dpp_min_i32_step<0x112, 0xf>(v);
-    v = dpp_min_i32_step<0x114, 0xf>(v);
-    v = dpp_min_i32_step<0x118, 0xf>(v);
-    v = dpp_min_i32_step<0x142, 0xa>(v);
-    v = dpp_min_i32_step<0x143, 0xc>(v);
-    return __builtin_amdgcn_readlane(v, 63);
-}
-
-// ---------------------------------------------------------------------------------------------
-// A table entry of the DP: 64 bits wherever it is stored or handed over, in one of two representations.
-//
-// Scaled (SC = true): the pair (m, r) stands for the sum over all alignments that end in the cell of
-// 2^(-cost * log2(e)/gamma), as m * 2^-r with a float32 mantissa and an int32 scale.  In this form the
-// recurrence R = d + softmin(three predecessors) is linear: the sum of the three neighbours' values,
-// brought to the smallest of their scales, times 2^-t, t = d * log2(e)/gamma.  The chain from one step to
-// the next is a lane shift and a fused multiply-add for the mantissas and, ahead of it, a lane shift, a
-// minimum and an addition for the scales: no transcendental, no float64.  (Only 2^-t needs one, of the
-// fraction of t alone, and it is off the chain.)  A lone wavefront takes 66 cycles per step for it against
-// 115 for the logarithmic form: 15 plain 4-cycle instructions, where that one has 18 among them 3
-// transcendentals, in one dependent chain.
-//   Accuracy: every step rounds the mantissa three times and 2^-fraction once, each 2^-24 relative, i.e.
-//   about 10^-7 absolute in the exponent; the logarithmic form's float32 exp2, log2 and sum cost it the same.
-//   Scales are integers, so sums of costs carry no rounding at all, however large they grow.
-//   Range: mantissas are brought back to [1/2, 1) once in 16 steps (renorm), in between they move by at most
-//   2^-16 .. 2^26 (an edge value of the neighbouring band, taken as it is, doubles that), so a term
-//   whose factor 2^(difference of scales) underflows is below 2^-70 of the sum.  Scale arithmetic
-//   saturates: a cell without alignments has m = 0 and a scale that only grows.
-// Logarithmic (SC = false): the float64 value of R in units of gamma*ln2.  Needed where scales could pass 2^31
-// (scaled_fits): unnormalised features with a tiny gamma.
-// ---------------------------------------------------------------------------------------------
-template <bool SC> struct Cell;
-template <> struct Cell<true> { float m; int r; };
-template <> struct Cell<false> { double v; };
-
-template <bool SC> __device__ __forceinline__ uint64_t pack(const Cell<SC> &c)
-{
-    if constexpr (SC)
-        return ((uint64_t)(unsigned)c.r << 32) | __float_as_uint(c.m);
-    else
-        return (uint64_t)__double_as_longlong(c.v);
-}
-template <bool SC> __device__ __forceinline__ Cell<SC> unpack(uint64_t bits)
-{
-    if constexpr (SC)
-        return {__uint_as_float((unsigned)bits), (int)(bits >> 32)};
-    else
-        return {__longlong_as_double((long long)bits)};
-}
-template <bool SC> __device__ __forceinline__ Cell<SC> cell_none() { return unpack<SC>(kBigBits); }
-template <bool SC> __device__ __forceinline__ Cell<SC> cell_origin()  // the cell before the first: cost 0, one alignment
-{
-    if constexpr (SC)
-        return {1.0f, 0};
-    else
-        return {0.0};
-}
-template <bool SC> __device__ __forceinline__ Cell<SC> cell_shr1(const Cell<SC> &c, uint64_t fill)
-{
-    const Cell<SC> f = unpack<SC>(fill);
-    if constexpr (SC)
-        return {__int_as_float(lane_shr1_i32(__float_as_int(c.m), __float_as_int(f.m))), lane_shr1_i32(c.r, f.r)};
-    else
-        return {lane_shr1(c.v, f.v)};
-}
-template <bool SC> __device__ __forceinline__ Cell<SC> cell_shl1(const Cell<SC> &c, uint64_t fill)
-{
-    const Cell<SC> f = unpack<SC>(fill);
-    if constexpr (SC)
-        return {__int_as_float(lane_shl1_i32(__float_as_int(c.m), __float_as_int(f.m))), lane_shl1_i32(c.r, f.r)};
-    else
-        return {lane_shl1(c.v, f.v)};
-}
-__device__ __forceinline__ int sat_add(int a, int b) { return __builtin_elementwise_add_sat(a, b); }
-__device__ __forceinline__ int sat_sub(int a, int b) { return __builtin_elementwise_sub_sat(a, b); }
-template <bool SC> __device__ __forceinline__ void renorm(Cell<SC> &c)
-{
-    if constexpr (SC) {
-        c.r = sat_sub(c.r, __builtin_amdgcn_frexp_expf(c.m));
-        c.m = __builtin_amdgcn_frexp_mantf(c.m);
-    }
-}
-// 2^-t as (w, k): w * 2^-k.  t >= 0; the marker of cells outside the grid (kBigCost) gives k = INT_MAX.
-__device__ __forceinline__ void cost_factor(float t, float &w, int &k)
-{
-    w = __builtin_amdgcn_exp2f(-__builtin_amdgcn_fractf(t));
-    asm("v_cvt_i32_f32 %0, %1" : "=v"(k) : "v"(t));  // truncates, saturates
-}
-// value of a scaled entry in table units
-__device__ __forceinline__ double cell_log2(const Cell<true> &c) { return (double)c.r - (double)__builtin_amdgcn_logf(c.m); }
-__device__ __forceinline__ double cell_log2(const Cell<false> &c) { return c.v; }
-
-// Do all scales stay within int32?  mx: largest ||x_i||^2 and ||y_j||^2.  No cost exceeds 2 (mx.x + mx.y), and a cell is
-// reached by an alignment of at most max(i,j) + 1 cells, so scales stay below the product; the rest of the
-// int32 range is for the entropy of the alignments (< 1.6 (N+M)) and the differences that are formed.
-// (not-a-number and infinite norms: no)
-__device__ __forceinline__ bool scaled_fits(const Params &p, float2 mx)
-{
-    return 2.0 * ((double)mx.x + (double)mx.y) * (double)p.c2f * (double)(max(p.N, p.M) + 2) < 2.0e9;
+    int lo = __builtin_amdgcn_readlane(__double2loint(v), src);
+    int hi = __builtin_amdgcn_readlane(__double2hiint(v), src);
+    return __hiloint2double(hi, lo);
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -38,6 +38,7 @@
 
 namespace sdtw {
 
+constexpr int kPeekStep = 24;      // step of a macro-step at which the next boundary values are requested
 constexpr int kRingCols = 128;     // four phases of 32 steps
 constexpr int kRingStride = 129;   // floats per band row in LDS (odd: lanes hit distinct banks)
 constexpr int kRingFloats = kBandRows * kRingStride;
@@ -60,18 +61,6 @@ constexpr int kHandDoubles = kHandRing + kBandRows + kBlk;
 // state at the start of every macro-step (1/16 of R) and the backward recomputes each macro-step of
 // R before it uses it - from the cost block that is in the ring anyway, in either mode.
 constexpr bool dp_recompute(int /*kch*/, int slots) { return slots == 4; }
-// Shapes whose sweeps may use scaled table entries (Cell, device_core.h).  The scaled chain is shorter but gives a
-// SIMD as much to issue, so it pays where a consumer has a SIMD to itself and waits for its own results; in
-// the 4-band workgroups, whose consumer shares its SIMD with the producers, it does not (B = 32, L = 8192: 11.0 ms
-// logarithmic, 11.3 ms scaled), nor where the producer is what a macro-step waits for (D > 128: 670 against
-// 682 us at B = 16, L = 512, D = 200).
-constexpr bool may_scale(int kch, int slots) { return slots != 4 && kch != 0; }
-// In those shapes a producer fetches the band's incoming edge values (Courier) and the consumer, whose chain
-// everything waits for, issues no load; elsewhere the producers are the ones that are waited for and the consumer
-// fetches (B = 32, L = 8192: 11.3 ms against 14.0 ms).
-constexpr bool consumer_fetches(int kch, int slots) { return !may_scale(kch, slots); }
-// step of a macro-step at which such a consumer asks for the next one's values
-constexpr int kPeekStep = 24;
 constexpr float kBigCost = 3.0e38f;  // cost of a cell outside the grid
 constexpr int kStatusTimeoutDp = 6;  // SDTW_ERR_TIMEOUT
 
@@ -106,84 +95,6 @@ __device__ __forceinline__ void softmin3_parts(double a, double b, double c, dou
     L = __builtin_amdgcn_logf(S);
 }
 
-// One step of the chain.  Soft: the soft-minimum of the three neighbours, i.e. the cell without its own
-// cost; the scaled form is the sum of the neighbours at the smallest of their scales (Cell, device_core.h).
-template <bool SC> struct Soft;
-template <> struct Soft<true> { float s; int r; };
-template <> struct Soft<false> { double m; float L; };
-template <bool SC> __device__ __forceinline__ Soft<SC> soft3(const Cell<SC> &diag, const Cell<SC> &up, const Cell<SC> &left)
-{
-    if constexpr (SC) {
-        const int r = min(min(up.r, left.r), diag.r);
-        const float fl = __builtin_amdgcn_ldexpf(1.0f, sat_sub(r, left.r)), fd = __builtin_amdgcn_ldexpf(1.0f, sat_sub(r, diag.r)),
-                    fu = __builtin_amdgcn_ldexpf(1.0f, sat_sub(r, up.r));
-        return {fmaf(up.m, fu, fmaf(left.m, fl, diag.m * fd)), r};
-    } else {
-        Soft<SC> q;
-        softmin3_parts(diag.v, up.v, left.v, q.m, q.L);
-        return q;
-    }
-}
-// the cell with its own cost: dc = d * log2(e)/gamma (scaled), or d (logarithmic, c2d = log2(e)/gamma)
-template <bool SC> __device__ __forceinline__ Cell<SC> add_cost(const Soft<SC> &q, float dc, double c2d)
-{
-    if constexpr (SC) {
-        float w;
-        int k;
-        cost_factor(dc, w, k);
-        return {q.s * w, sat_add(q.r, k)};
-    } else {
-        // every addition that builds the table is float64: a float32 rounding here would
-        // differ between the two sweeps and add up along the alignment path
-        return {fma((double)dc, c2d, q.m) - (double)q.L};
-    }
-}
-// both at once, with the cost's factor in the neighbours' (an instruction and a link of the chain less)
-template <bool SC>
-__device__ __forceinline__ Cell<SC> dp_cell(const Cell<SC> &diag, const Cell<SC> &up, const Cell<SC> &left, float dc, double c2d)
-{
-    if constexpr (SC) {
-        float w;
-        int k;
-        cost_factor(dc, w, k);
-        const int r = min(min(up.r, left.r), diag.r);
-        const float fl = __builtin_amdgcn_ldexpf(w, sat_sub(r, left.r)), fd = __builtin_amdgcn_ldexpf(w, sat_sub(r, diag.r)),
-                    fu = __builtin_amdgcn_ldexpf(w, sat_sub(r, up.r));
-        return {fmaf(up.m, fu, fmaf(left.m, fl, diag.m * fd)), sat_add(r, k)};
-    } else {
-        return add_cost<SC>(soft3<SC>(diag, up, left), dc, c2d);
-    }
-}
-// Steps of a macro-step after which the chain's value is renormalised (Cell): two consecutive ones of every 16,
-// since an alignment may pass from one step to the next but one (a diagonal move) and must not slip past.
-constexpr bool renorm_after(int u) { return (u & 15) >= 14; }
-
-// Does this call's sweep use scaled entries?  From the norms' maxima the launch before left in Params::cmax: every
-// workgroup reads them all (beside the first loads it waits for anyway).  Two halves around a barrier.
-template <int THREADS> __device__ __forceinline__ void find_cost_maximum(const Params &p, float2 *wave_max)
-{
-    float2 mx = make_float2(0.f, 0.f);
-#pragma unroll 4
-    for (int i = threadIdx.x; i < p.nslots; i += THREADS) {
-        const float2 v = p.cmax[i];
-        mx.x = fmaxf(mx.x, v.x);
-        mx.y = fmaxf(mx.y, v.y);
-    }
-    mx.x = wave_max_f32(mx.x);
-    mx.y = wave_max_f32(mx.y);
-    if ((threadIdx.x & 63) == 0) wave_max[threadIdx.x >> 6] = mx;
-}
-template <int THREADS> __device__ __forceinline__ bool use_scaled(const Params &p, const float2 *wave_max)
-{
-    float2 mx = wave_max[0];
-#pragma unroll
-    for (int i = 1; i < THREADS / 64; ++i) {
-        mx.x = fmaxf(mx.x, wave_max[i].x);
-        mx.y = fmaxf(mx.y, wave_max[i].y);
-    }
-    return __builtin_amdgcn_readfirstlane((int)(p.nslots > 0 && scaled_fits(p, mx))) != 0;
-}
-
 __device__ __forceinline__ float comp4(const float4 &v, int c)
 {
     return c == 0 ? v.x : (c == 1 ? v.y : (c == 2 ? v.z : v.w));
@@ -197,7 +108,7 @@ __device__ __forceinline__ float comp4(const float4 &v, int c)
 // never waits again; other bands notice the recorded status and stop waiting too, so every
 // kernel exits.
 // ---------------------------------------------------------------------------------------------
-__device__ __forceinline__ uint64_t resolve_boundary(const Params &p, const unsigned long long *row, int jj, bool need,
+__device__ __forceinline__ double resolve_boundary(const Params &p, const unsigned long long *row, int jj, bool need,
                                                    int lane, bool &gave_up, unsigned long long bits)
 {
     unsigned spins = 0;
@@ -213,64 +124,24 @@ __device__ __forceinline__ uint64_t resolve_boundary(const Params &p, const unsi
             gave_up = true;
             break;
         }
-        __builtin_amdgcn_s_sleep(1);
+        __builtin_amdgcn_s_sleep(4);
         if (need) bits = __hip_atomic_load(row + jj, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    return bits;
+    return __longlong_as_double((long long)bits);
 }
 
 __device__ __forceinline__ unsigned long long peek_boundary(const unsigned long long *row, int jj, bool need)
 {
-    unsigned long long bits = kBigBits;
+    unsigned long long bits = (unsigned long long)__double_as_longlong(kBig);
     if (need) bits = __hip_atomic_load(row + jj, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     return bits;
 }
 
-__device__ __forceinline__ void publish_boundary(unsigned long long *row, int j, uint64_t v)
+__device__ __forceinline__ void publish_boundary(unsigned long long *row, int j, double v)
 {
-    __hip_atomic_store(row + j, (unsigned long long)v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(row + j, (unsigned long long)__double_as_longlong(v), __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
 }
-
-// ---------------------------------------------------------------------------------------------
-// Courier: the band's edge values between memory and LDS.  The consumer publishes what a macro-step left behind as
-// soon as it is through with it (left to a producer, which does it behind the barrier and at a lower priority, every hop
-// takes longer: 427 -> 449 us at B = 32, L = 1024).  What the coming macro-step needs is fetched, double-buffered by
-// the parity of the macro-step, by a producer where may_scale() holds and by the consumer elsewhere.
-//   forward (DIR = +1): in: the row above, lane l < 32 brings column 32*sg + l; out: the band's last row, lanes
-//     32 .. 63 publish columns 32*sg - 63 + (l - 32)
-//   reverse (DIR = -1): in: the row below, lane l >= 32 brings column 32*sg - 63 + (l - 32), which lane 63 meets
-//     at step l - 32; out: the band's first row, lanes 0 .. 31 publish columns 32*sg + l
-// ---------------------------------------------------------------------------------------------
-template <int DIR> struct Courier {
-    const unsigned long long *in = nullptr;
-    unsigned long long *out = nullptr;
-    bool has_in = false, emit = false, gave_up = false;
-    unsigned long long bits = kBigBits;
-
-    __device__ __forceinline__ static int in_col(int sg, int lane) { return sg * kBlk + (DIR > 0 ? lane : lane - kBlk - (kBandRows - 1)); }
-    __device__ __forceinline__ static int out_col(int sg, int lane) { return sg * kBlk + (DIR > 0 ? lane - kBlk - (kBandRows - 1) : lane); }
-    __device__ __forceinline__ bool need(const Params &p, int sg, int lane) const
-    {
-        const int j = in_col(sg, lane);
-        return has_in && (DIR > 0 ? lane < kBlk : lane >= kBlk) && j >= 0 && j < p.M;
-    }
-    __device__ __forceinline__ void peek(const Params &p, int sg, int lane)
-    {
-        if (has_in) bits = peek_boundary(in, in_col(sg, lane), need(p, sg, lane));
-    }
-    // (dst: edge_in of the macro-step's parity; without a neighbour it holds kBigBits from the start)
-    __device__ __forceinline__ void deliver(const Params &p, uint64_t *dst, int sg, int lane)
-    {
-        if (!has_in) return;
-        const uint64_t v = resolve_boundary(p, in, in_col(sg, lane), need(p, sg, lane), lane, gave_up, bits);
-        if (DIR > 0 ? lane < kBlk : lane >= kBlk) dst[lane & (kBlk - 1)] = v;
-    }
-    __device__ __forceinline__ void publish(const Params &p, const uint64_t *src, int sg, int lane) const
-    {
-        const int j = out_col(sg, lane);
-        if (emit && (DIR > 0 ? lane >= kBlk : lane < kBlk) && j >= 0 && j < p.M) publish_boundary(out, j, src[lane & (kBlk - 1)]);
-    }
-};
 
 // ---------------------------------------------------------------------------------------------
 // Producer side: cost blocks into the ring.
@@ -353,10 +224,8 @@ __device__ __forceinline__ void load_cost_block(float4 (&v)[4], const float *__r
     }
 }
 
-// cs: what the costs are multiplied by (Params::c2f for scaled tables, else 1); kBigCost stays the marker it is
-__device__ __forceinline__ void store_cost_block(float *ring, const float4 (&v)[4], int rb, int cb, int lane, float cs)
+__device__ __forceinline__ void store_cost_block(float *ring, const float4 (&v)[4], int rb, int cb, int lane)
 {
-    auto cost = [&](int it, int e) { return cs == 1.0f ? comp4(v[it], e) : fminf(comp4(v[it], e) * cs, kBigCost); };
     const int c4 = (lane & 7) * 4;
     const int phase = (cb + rb) & 3;
     if (phase != 3) {  // no entry of the block wraps around the ring: constant offsets from the lane's base
@@ -364,7 +233,7 @@ __device__ __forceinline__ void store_cost_block(float *ring, const float4 (&v)[
 #pragma unroll
         for (int it = 0; it < 4; ++it)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) lane_base[8 * it * kRingStride + 8 * it + e] = cost(it, e);
+            for (int e = 0; e < 4; ++e) lane_base[8 * it * kRingStride + 8 * it + e] = comp4(v[it], e);
         return;
     }
 #pragma unroll
@@ -373,12 +242,12 @@ __device__ __forceinline__ void store_cost_block(float *ring, const float4 (&v)[
         float *rowp = ring + (32 * rb + r) * kRingStride;
         const int base = 32 * (cb + rb) + c4 + r;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) rowp[(base + e) & (kRingCols - 1)] = cost(it, e);
+        for (int e = 0; e < 4; ++e) rowp[(base + e) & (kRingCols - 1)] = comp4(v[it], e);
     }
 }
 
 // Any-D cost block straight from x and y (fused mode when D > 128).
-__device__ __forceinline__ void generic_block(const Params &p, int b, float *ring, int rb, int cb, int row0, int lane, float cs)
+__device__ __forceinline__ void generic_block(const Params &p, int b, float *ring, int rb, int cb, int row0, int lane)
 {
     float out[16];
     const int i0 = row0 + 32 * rb, j0 = 32 * cb;
@@ -386,7 +255,7 @@ __device__ __forceinline__ void generic_block(const Params &p, int b, float *rin
                min(i0, p.N - 1), max(0, min(j0, p.M - 1)), lane, out);
     floatx16 acc;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) acc[i] = out[i] * cs;
+    for (int i = 0; i < 16; ++i) acc[i] = out[i];
     // when the block origin had to be clamped the whole block lies outside the grid
     const bool origin_ok = (i0 < p.N) && (j0 >= 0) && (j0 < p.M);
     store_block_acc(ring, acc, rb, cb, row0, origin_ok ? p.N : 0, p.M, p.window, lane);
@@ -399,15 +268,6 @@ template <int DIR> __device__ __forceinline__ int blk_rb(int which) { return DIR
 template <int DIR> __device__ __forceinline__ int blk_cb(int sg, int which)
 {
     return DIR > 0 ? sg + which : sg - 2 - which;
-}
-
-// A norm in the units of the ring.  Its own rounding, everywhere: contracted into the sum of the two norms in one
-// producer and not in the other, the two sweeps would see different costs (E off by 10^-4 along a path of
-// 100 cells).
-__device__ __forceinline__ float scale_norm(float n, float cs)
-{
-#pragma clang fp contract(off)
-    return n * cs;
 }
 
 // Matrix-core producer for D <= 16*KG (KG = 1, 2, 4, 8 groups of 16 features).
@@ -432,7 +292,6 @@ template <int KG, int DIR, int W0, int NW> struct HalfProducer {
     half8 xa[2][2][KG];     // [row block][piece][group]
     half8 ybuf[NBUF][2];    // [stage][piece]
     float yn_c[2], yis_c[2];  // ||y_c||^2 and 1/scale of this lane's column, for the blocks of the macro-step
-    float cs;               // the costs come out multiplied by this (Params::c2f for scaled tables, else 1)
     bool one_piece;         // the operands are float16 / bfloat16 values: their first piece is all of them (Params::pieces)
 
     __device__ __forceinline__ int ycol(const Params &p, int cb, int lane) const
@@ -448,10 +307,9 @@ template <int KG, int DIR, int W0, int NW> struct HalfProducer {
     }
     // x pieces of the band, and the per-row table (||x_r||^2, -2/scale_r) in LDS
     __device__ __forceinline__ void init(const Params &p, const uint16_t *xh, const float *xnb, const float *xisb,
-                                         float2 *rowtab, int row0, int lane, float cost_scale)
+                                         float2 *rowtab, int row0, int lane)
     {
         one_piece = p.pieces == 1;
-        cs = cost_scale;
 #pragma unroll
         for (int rb = 0; rb < 2; ++rb) {
             if (!owns_rb(rb)) continue;
@@ -462,7 +320,7 @@ template <int KG, int DIR, int W0, int NW> struct HalfProducer {
                 xa[rb][0][g] = *reinterpret_cast<const half8 *>(r + 32 * g);
                 xa[rb][1][g] = *reinterpret_cast<const half8 *>(r + 32 * g + 16);
             }
-            if (lane < 32) rowtab[32 * rb + lane] = make_float2(scale_norm(xnb[row], cs), -2.0f * xisb[row] * cs);
+            if (lane < 32) rowtab[32 * rb + lane] = make_float2(xnb[row], -2.0f * xisb[row]);
         }
     }
     __device__ __forceinline__ floatx16 mfma3(floatx16 acc, int rb, int g, const half8 &k1, const half8 &k2) const
@@ -474,7 +332,7 @@ template <int KG, int DIR, int W0, int NW> struct HalfProducer {
         }
         return acc;
     }
-    // acc (scaled inner products) -> cost block in the ring:  cs * (||x||^2 + ||y||^2 - 2 <x,y>), clamped at 0
+    // acc (scaled inner products) -> cost block in the ring:  d = ||x||^2 + ||y||^2 - 2 <x,y>, clamped at 0
     __device__ __forceinline__ void finish(const Params &p, float *ring, const float2 *rowtab, floatx16 acc,
                                            int rb, int cb, float ync, float yisc, int row0, int lane) const
     {
@@ -499,7 +357,7 @@ template <int KG, int DIR, int W0, int NW> struct HalfProducer {
         floatx16 acc = zero16();
 #pragma unroll
         for (int g = 0; g < KG; ++g) acc = mfma3(acc, rb, g, ybuf[g][0], ybuf[g][1]);
-        finish(p, ring, rowtab, acc, rb, cb, scale_norm(ynb[col], cs), yisb[col], row0, lane);
+        finish(p, ring, rowtab, acc, rb, cb, ynb[col], yisb[col], row0, lane);
         __builtin_amdgcn_sched_barrier(0);
     }
     // stage buffers and column norms for the first macro-step `sg`
@@ -511,21 +369,20 @@ template <int KG, int DIR, int W0, int NW> struct HalfProducer {
 #pragma unroll
         for (int i = 0; i < NW; ++i) {
             const int col = ycol(p, blk_cb<DIR>(sg, W0 + i), lane);
-            yn_c[i] = scale_norm(ynb[col], cs);
+            yn_c[i] = ynb[col];
             yis_c[i] = yisb[col];
         }
     }
-    // the blocks of macro-step sg; late() is called shortly before the end
-    template <class Late>
+    // the blocks of macro-step sg
     __device__ __forceinline__ void run(const Params &p, const uint16_t *yh, const float *ynb, const float *yisb,
-                                        float *ring, const float2 *rowtab, int sg, int row0, int lane, Late &&late)
+                                        float *ring, const float2 *rowtab, int sg, int row0, int lane)
     {
         const int sgn = sg + DIR;  // next macro-step
         float nyn[2], nyis[2];
 #pragma unroll
         for (int i = 0; i < NW; ++i) {
             const int col = ycol(p, blk_cb<DIR>(sgn, W0 + i), lane);
-            nyn[i] = ynb[col];  // (scaled below: a product here would wait for the load)
+            nyn[i] = ynb[col];
             nyis[i] = yisb[col];
         }
         auto reload = [&](int q) {  // refill the buffer of stage q with the stage NBUF stages later
@@ -550,7 +407,6 @@ template <int KG, int DIR, int W0, int NW> struct HalfProducer {
                 __builtin_amdgcn_sched_barrier(0);
                 if (g < kEarly) reload(q);
             }
-            if (w == NW - 1) late();
             finish(p, ring, rowtab, acc, rb, blk_cb<DIR>(sg, which), yn_c[w], yis_c[w], row0, lane);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -558,7 +414,7 @@ template <int KG, int DIR, int W0, int NW> struct HalfProducer {
         }
 #pragma unroll
         for (int i = 0; i < NW; ++i) {
-            yn_c[i] = scale_norm(nyn[i], cs);
+            yn_c[i] = nyn[i];
             yis_c[i] = nyis[i];
         }
     }
@@ -840,8 +696,6 @@ __global__ __launch_bounds__(256) void cost_tensor_prep_kernel(Params p)
         }
     }
     __syncthreads();
-    // (rows of a tile's edge are repeated inside it: they change no maximum)
-    if (p.nslots > 0) store_cost_maximum(p, blk, tid < 128 ? xtab[tid].x : 0.f, tid < 32 * CB ? ytab[tid].x : 0.f);
     float xn_r[16], m2is_r[16];
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
@@ -858,19 +712,18 @@ __global__ __launch_bounds__(256) void cost_tensor_prep_kernel(Params p)
 // ---------------------------------------------------------------------------------------------
 template <int SLOTS> struct WgShared {
     float ring[SLOTS][kRingFloats];
-    uint64_t edge_in[SLOTS][2][kBlk];  // boundary values of the macro-steps (by parity), one per step
-    uint64_t ftop[SLOTS][kBlk];     // backward with recomputation: the forward's row above the band
+    double edge_in[SLOTS][kBlk];  // boundary values of the current macro-step, one per step
+    double ftop[SLOTS][kBlk];     // backward with recomputation: the forward's row above the band
     float2 rowtab[SLOTS][kBandRows];  // per band row: (||x_r||^2, -2/scale_r) for the cost epilogue
     int simd_count[4];
-    float2 wave_max[12];  // largest norms each wavefront saw (find_cost_maximum)
     int blk_dead[SLOTS][2];  // reverse sweep: the E blocks completed by macro-step sg hold no non-zero (indexed by sg & 1)
 };
 
 // Values the band's edge row (last row in the forward sweep, first in the reverse sweep) produced
-// in a macro-step, one per step, for the neighbouring band: 64-bit entries [SLOTS][kEdgeOut] in LDS.  Every
-// lane writes its value each step; only the edge lane's address points into the first 32, the others
-// write to slots of their own behind them.  (Kept as an
-// object of its own, so that these stores are known not to touch the ring or the incoming boundary values.)
+// in the current macro-step, one per step, for the neighbouring band: double[SLOTS][kEdgeOut] in
+// LDS.  Every lane writes its value each step; only the edge lane's address points into [0,32),
+// the others write to slots of their own behind it.  (Kept as an object of its own, so that these
+// stores are known not to touch the ring or the incoming boundary values.)
 constexpr int kEdgeOut = kBlk + kBandRows + kBlk;
 
 // Groups the wavefronts that share a SIMD as consumer (0) and producers (1, 2) of one band slot.
@@ -913,8 +766,8 @@ __device__ __forceinline__ void chain_role(int w, int &producer, int &slot)
 // ---------------------------------------------------------------------------------------------
 template <int KCH, int SLOTS, int NPROD>
 __device__ __forceinline__ void forward_dp_body(const Params &p, float *__restrict__ value, WgShared<SLOTS> &sh,
-                                                unsigned &ticket_s, uint64_t (&edge_out)[SLOTS][kEdgeOut],
-                                                uint64_t (&hand)[kHandDoubles])
+                                                unsigned &ticket_s, double (&edge_out)[SLOTS][kEdgeOut],
+                                                double (&hand)[kHandDoubles])
 {
     static_assert(SLOTS == 4 || SLOTS == 2 || SLOTS == 1, "supported workgroup shapes");
     static_assert(NPROD == 1 || (NPROD == 2 && KCH > 0), "two producers only split MFMA work");
@@ -922,13 +775,12 @@ __device__ __forceinline__ void forward_dp_body(const Params &p, float *__restri
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 
     if (threadIdx.x == 0) ticket_s = atomicAdd(&p.hdr->fwd_ticket, 1u);
-    if constexpr (may_scale(KCH, SLOTS)) find_cost_maximum<kThreads>(p, sh.wave_max);
     for (int e = threadIdx.x; e < SLOTS * kRingFloats; e += kThreads) (&sh.ring[0][0])[e] = kBigCost;
     int producer, slot;  // producer: 0 = consumer, 1.. = producer number
     if constexpr (SLOTS == 4) {
         elect_role(sh, lane, w, 1 + NPROD, producer, slot);  // contains two barriers
     } else if constexpr (SLOTS == 2) {
-        for (int e = threadIdx.x; e < kHandDoubles; e += kThreads) hand[e] = kBigBits;
+        for (int e = threadIdx.x; e < kHandDoubles; e += kThreads) hand[e] = kBig;
         chain_role(w, producer, slot);
         __syncthreads();
     } else {
@@ -961,10 +813,6 @@ __device__ __forceinline__ void forward_dp_body(const Params &p, float *__restri
         }
         rg = sweep_range(p, k * kBandRows, k * kBandRows, nl, ml);
     }
-    bool scaled = false;
-    if constexpr (may_scale(KCH, SLOTS)) scaled = use_scaled<kThreads>(p, sh.wave_max);
-    if (threadIdx.x == 0 && ticket == 0) p.hdr->scaled = scaled ? 1 : 0;  // for the kernels that read the tables
-    const float cs = scaled ? p.c2f : 1.0f;
     const bool live = (k < p.nbands) && (b < p.B) && rg.hi >= rg.lo;
     // chained pair: the second band does macro-step sg in workgroup iteration sg - rg.lo + kChainLag
     const int lag = (SLOTS == 2) ? kChainLag * slot : 0;
@@ -992,95 +840,74 @@ __device__ __forceinline__ void forward_dp_body(const Params &p, float *__restri
     const uint16_t *xh = p.xh + bb * p.xh_stride, *yh = p.yh + bb * p.yh_stride;
     float2 *rowtab = sh.rowtab[slot];
 
-    // chained pair: slot 0's last row reaches slot 1 through LDS (hand), and memory besides, where alignment_kernel
-    // looks for the columns that can hold a non-zero E
-    const bool row_from_lds = SLOTS == 2 && slot == 1;
-    constexpr bool kGet = consumer_fetches(KCH, SLOTS);
-
-    Courier<+1> cour;
-    {
-        const int kc = live ? k : 0;
-        cour.in = p.brow + ((size_t)bb * p.nbands + (kc > 0 ? kc - 1 : 0)) * M;
-        cour.out = p.brow + ((size_t)bb * p.nbands + kc) * M;
-        cour.has_in = live && k > 0 && !row_from_lds;
-        cour.emit = live && k + 1 < p.nbands;
-    }
     if (producer) {
         // ------------------------------------------------------------------ producer wavefront
-        // start(): what the first macro-step needs; work(sg, late): the blocks of macro-step sg.  courier: this wavefront
-        // carries the edge values
-        auto produce = [&](bool courier, auto &&start, auto &&work) {
-            if (live) {
-                if (!kGet && courier) {
-                    (&sh.edge_in[slot][0][0])[lane] = kBigBits;
-                    cour.peek(p, rg.lo, lane);
+        if constexpr (KCH > 0 && NPROD == 2) {
+            // producer 1 makes (lower rows, sg), producer 2 makes (upper rows, sg+1)
+            auto body = [&](auto &mp, bool first_block) {
+                if (live) {
+                    mp.init(pl, xh, xnb, xisb, rowtab, row0, lane);
+                    if (first_block) mp.block_now(pl, yh, ynb, yisb, ring, rowtab, 0, rg.lo, row0, lane);
+                    mp.prime(pl, yh, ynb, yisb, rg.lo, lane);
                 }
-                start();
-                if (!kGet && courier) cour.deliver(p, sh.edge_in[slot][kGet ? 0 : rg.lo & 1], rg.lo, lane);
+                __syncthreads();
+                for (int it = 0; it < niter; ++it) {
+                    const int sg = rg.lo + it - lag;
+                    if (live && sg >= rg.lo && sg <= rg.hi) mp.run(pl, yh, ynb, yisb, ring, rowtab, sg, row0, lane);
+                    __syncthreads();
+                }
+            };
+            if (producer == 1) {
+                HalfProducer<KCH, +1, 0, 1> mp;
+                body(mp, false);
+            } else {
+                HalfProducer<KCH, +1, 1, 1> mp;
+                body(mp, true);
+            }
+        } else if constexpr (KCH > 0) {
+            HalfProducer<KCH, +1, 0, 2> mp;
+            if (live) {
+                mp.init(pl, xh, xnb, xisb, rowtab, row0, lane);
+                mp.block_now(pl, yh, ynb, yisb, ring, rowtab, 0, rg.lo, row0, lane);  // (upper rows, first column block)
+                mp.prime(pl, yh, ynb, yisb, rg.lo, lane);
             }
             __syncthreads();
             for (int it = 0; it < niter; ++it) {
                 const int sg = rg.lo + it - lag;
-                                if (live && sg >= rg.lo && sg <= rg.hi) {
-                    work(sg, [&] { if (!kGet && courier) cour.peek(p, sg + 1, lane); });
-                    if (!kGet && courier) cour.deliver(p, sh.edge_in[slot][kGet ? 0 : (sg + 1) & 1], sg + 1, lane);
+                if (live && sg >= rg.lo && sg <= rg.hi) mp.run(pl, yh, ynb, yisb, ring, rowtab, sg, row0, lane);
+                __syncthreads();
+            }
+        } else if constexpr (KCH == 0) {
+            if (live) generic_block(pl, b, ring, 0, rg.lo, row0, lane);
+            __syncthreads();
+            for (int it = 0; it < niter; ++it) {
+                const int sg = rg.lo + it - lag;
+                if (live && sg >= rg.lo && sg <= rg.hi) {
+                    generic_block(pl, b, ring, 1, sg, row0, lane);
+                    generic_block(pl, b, ring, 0, sg + 1, row0, lane);
                 }
                 __syncthreads();
             }
-        };
-        if constexpr (KCH > 0 && NPROD == 2) {
-            // producer 1 makes (lower rows, sg), producer 2 makes (upper rows, sg+1)
-            if (producer == 1) {
-                HalfProducer<KCH, +1, 0, 1> mp;
-                produce(true,
-                        [&] {
-                            mp.init(pl, xh, xnb, xisb, rowtab, row0, lane, cs);
-                            mp.prime(pl, yh, ynb, yisb, rg.lo, lane);
-                        },
-                        [&](int sg, auto &&late) { mp.run(pl, yh, ynb, yisb, ring, rowtab, sg, row0, lane, late); });
-            } else {
-                HalfProducer<KCH, +1, 1, 1> mp;
-                produce(false,
-                        [&] {
-                            mp.init(pl, xh, xnb, xisb, rowtab, row0, lane, cs);
-                            mp.block_now(pl, yh, ynb, yisb, ring, rowtab, 0, rg.lo, row0, lane);
-                            mp.prime(pl, yh, ynb, yisb, rg.lo, lane);
-                        },
-                        [&](int sg, auto &&late) { mp.run(pl, yh, ynb, yisb, ring, rowtab, sg, row0, lane, late); });
-            }
-        } else if constexpr (KCH > 0) {
-            HalfProducer<KCH, +1, 0, 2> mp;
-            produce(true,
-                    [&] {
-                        mp.init(pl, xh, xnb, xisb, rowtab, row0, lane, cs);
-                        mp.block_now(pl, yh, ynb, yisb, ring, rowtab, 0, rg.lo, row0, lane);  // (upper rows, first column block)
-                        mp.prime(pl, yh, ynb, yisb, rg.lo, lane);
-                    },
-                    [&](int sg, auto &&late) { mp.run(pl, yh, ynb, yisb, ring, rowtab, sg, row0, lane, late); });
-        } else if constexpr (KCH == 0) {
-            produce(true, [&] { generic_block(pl, b, ring, 0, rg.lo, row0, lane, cs); },
-                    [&](int sg, auto &&late) {
-                        generic_block(pl, b, ring, 1, sg, row0, lane, cs);
-                        generic_block(pl, b, ring, 0, sg + 1, row0, lane, cs);
-                        late();
-                    });
         } else {
             const float *cost_b = p.cost + (size_t)bb * N * M;
             float4 pre[2][4];
-            produce(true,
-                    [&] {
-                        load_cost_block(pre[0], cost_b, 0, rg.lo, row0, Nl, Ml, M, p.window, p.vec_m != 0, lane);
-                        store_cost_block(ring, pre[0], 0, rg.lo, lane, cs);
-                        load_cost_block(pre[0], cost_b, 1, rg.lo, row0, Nl, Ml, M, p.window, p.vec_m != 0, lane);
-                        load_cost_block(pre[1], cost_b, 0, rg.lo + 1, row0, Nl, Ml, M, p.window, p.vec_m != 0, lane);
-                    },
-                    [&](int sg, auto &&late) {
-                        store_cost_block(ring, pre[0], 1, sg, lane, cs);
-                        store_cost_block(ring, pre[1], 0, sg + 1, lane, cs);
-                        late();
-                        load_cost_block(pre[0], cost_b, 1, sg + 1, row0, Nl, Ml, M, p.window, p.vec_m != 0, lane);
-                        load_cost_block(pre[1], cost_b, 0, sg + 2, row0, Nl, Ml, M, p.window, p.vec_m != 0, lane);
-                    });
+            if (live) {
+                load_cost_block(pre[0], cost_b, 0, rg.lo, row0, Nl, Ml, M, p.window, p.vec_m != 0, lane);
+                store_cost_block(ring, pre[0], 0, rg.lo, lane);
+                load_cost_block(pre[0], cost_b, 1, rg.lo, row0, Nl, Ml, M, p.window, p.vec_m != 0, lane);
+                load_cost_block(pre[1], cost_b, 0, rg.lo + 1, row0, Nl, Ml, M, p.window, p.vec_m != 0, lane);
+            }
+            __syncthreads();
+            for (int it = 0; it < niter; ++it) {
+                const int sg = rg.lo + it - lag;
+                if (live && sg >= rg.lo && sg <= rg.hi) {
+                    store_cost_block(ring, pre[0], 1, sg, lane);
+                    store_cost_block(ring, pre[1], 0, sg + 1, lane);
+                    load_cost_block(pre[0], cost_b, 1, sg + 1, row0, Nl, Ml, M, p.window, p.vec_m != 0, lane);
+                    load_cost_block(pre[1], cost_b, 0, sg + 2, row0, Nl, Ml, M, p.window, p.vec_m != 0, lane);
+                }
+                __syncthreads();
+            }
         }
         return;
     }
@@ -1092,76 +919,90 @@ __device__ __forceinline__ void forward_dp_body(const Params &p, float *__restri
     // CH: -1 = both neighbouring bands are reached through memory; 0 = the band below is the other
     // band of this workgroup (edge values go to the LDS hand-over ring); 1 = the band above is.
     // (Separate instances, so that each one reads and writes distinct LDS objects.)
-    auto consume = [&](auto chain_c, auto scaled_c) {
+    auto consume = [&](auto chain_c) {
     constexpr int CH = decltype(chain_c)::value;
-    constexpr bool SC = decltype(scaled_c)::value;
     const double c2d = p.c2d;  // log2(e)/gamma
-    Cell<SC> left = cell_none<SC>();                     // R[i][j-1]
-    Cell<SC> diag = cell_none<SC>();                     // R[i-1][j-1]; R[0,0] = 0 in the paper's indexing
-    if (k == 0 && lane == 0) diag = cell_origin<SC>();
+    bool gave_up = false;
+    double left = kBig;                                  // R[i][j-1]
+    double diag = (k == 0 && lane == 0) ? 0.0 : kBig;    // R[i-1][j-1]; R[0,0] = 0 in the paper's indexing
     const int kc = live ? k : 0;
+    const unsigned long long *brow_in = p.brow + ((size_t)bb * p.nbands + (kc > 0 ? kc - 1 : 0)) * M;
+    unsigned long long *brow_out = p.brow + ((size_t)bb * p.nbands + kc) * M;
     // RECOMP: the table is not stored; only the lane state at the start of every macro-step is
     // (checkpoints), and the backward kernel recomputes each macro-step of R from it.
     constexpr bool RECOMP = dp_recompute(KCH, SLOTS);
     // (table pointers are those of the band's macro-step 0; the table starts at macro-step table_base)
     const ptrdiff_t tb = table_base(p, kc);
-    uint64_t *Rk = RECOMP ? nullptr : p.R + (((size_t)bb * p.nbands + kc) * (size_t)p.nm_tab - tb) * kBlk * kBandRows;
-    uint64_t *Ck = RECOMP ? p.ckpt + (((size_t)bb * p.nbands + kc) * (size_t)p.nm_tab - tb) * 2 * kBandRows : nullptr;
+    double *Rk = RECOMP ? nullptr : p.R + (((size_t)bb * p.nbands + kc) * (size_t)p.nm_tab - tb) * kBlk * kBandRows;
+    double *Ck = RECOMP ? p.ckpt + (((size_t)bb * p.nbands + kc) * (size_t)p.nm_tab - tb) * 2 * kBandRows : nullptr;
     const int s_fin = (live && row0 + lane == Nl - 1) ? (Ml - 1 + lane) : -1;  // step of the pair's last cell
     const bool last_band = live && (k == (Nl - 1) / kBandRows);
-    uint64_t fin = 0;
+    double fin = 0.0;
+    const bool has_above = live && k > 0 && CH != 1;                // through memory
+    const bool emit_bottom = live && (k + 1 < p.nbands);             // the band's last row goes to memory
     const float *my_ring = ring + lane * kRingStride;
-    uint64_t *eo = edge_out[slot];
-    if (kGet && CH != 1 && live) {
-        (&sh.edge_in[slot][0][0])[lane] = kBigBits;
-        cour.peek(p, rg.lo, lane);
-        cour.deliver(p, sh.edge_in[slot][kGet ? 0 : rg.lo & 1], rg.lo, lane);
+    double *top = sh.edge_in[slot];
+    double *eo = edge_out[slot];
+
+    // row above the band for the first macro-step: lane l < 32 brings column 32*rg.lo + l
+    // (the cells left of it are outside the grid or outside the window: the lane state starts as kBig)
+    if constexpr (CH != 1) {
+        double t0 = kBig;
+        if (has_above) {
+            const int j0 = rg.lo * kBlk + lane;
+            const bool need = lane < kBlk && j0 < M;
+            t0 = resolve_boundary(p, brow_in, j0, need, lane, gave_up, peek_boundary(brow_in, j0, need));
+        }
+        if (lane < kBlk) top[lane] = t0;
     }
     __syncthreads();
 
     for (int it = 0; it < niter; ++it) {
         const int sg = rg.lo + it - lag;
         if (live && sg >= rg.lo && sg <= rg.hi) {
+            unsigned long long nxt_bits = (unsigned long long)__double_as_longlong(kBig);
+            const int jn = (sg + 1) * kBlk + lane;
+            const bool need_n = has_above && lane < kBlk && jn < M;
             const float *rd = my_ring + (sg & 3) * kBlk;
+            // the macro-step's 32 cost values, read in one batch: read one per step they sit between the
+            // steps' LDS stores, which they may not overtake, and each costs the chain a wait
+            float dcv[kBlk];
+#pragma unroll
+            for (int u = 0; u < kBlk; ++u) dcv[u] = rd[u];
             // The row above, column 32*sg + u at step u: from the incoming boundary values, or from
             // the hand-over ring, where the band above put column c at slot (c + 63) mod 128.
-            const uint64_t *top0 = sh.edge_in[slot][kGet ? 0 : sg & 1], *top1 = top0 + 1;  // step 0, steps 1..31
+            const double *top0 = top, *top1 = top + 1;  // step 0, steps 1..31
             if constexpr (CH == 1) {
                 top0 = hand + ((sg + 1) & 3) * kBlk + (kBlk - 1);
                 top1 = hand + ((sg + 2) & 3) * kBlk;
             }
-            // The macro-step's 32 cost values and its row above, read in one batch: read one per step they sit
-            // between the steps' LDS stores, which they may not overtake, and each costs the chain a wait.
-            float dcv[kBlk];
-            constexpr bool kBatchTop = SC;  // (behind the longer logarithmic step a read per step costs nothing)
-            [[maybe_unused]] uint64_t tv[kBlk];
-#pragma unroll
-            for (int u = 0; u < kBlk; ++u) {
-                dcv[u] = rd[u];
-                if (kBatchTop) tv[u] = u == 0 ? top0[0] : top1[u - 1];
-            }
-            if constexpr (kBatchTop) __builtin_amdgcn_sched_barrier(0);
             // Where this macro-step's values go: lane 63's are the band's last row (column
             // 32*sg + u - 63 at step u), the other lanes write to slots of their own.
-            uint64_t *my_eo = eo + ((lane == kBandRows - 1) ? 0 : kBlk + lane);
+            double *my_eo = eo + ((lane == kBandRows - 1) ? 0 : kBlk + lane);
             if constexpr (CH == 0) my_eo = hand + ((lane == kBandRows - 1) ? (sg & 3) * kBlk : kHandRing + lane);
-            uint64_t *Rs = RECOMP ? nullptr : Rk + (size_t)sg * kBlk * kBandRows;
+            double *Rs = RECOMP ? nullptr : Rk + (size_t)sg * kBlk * kBandRows;
             if constexpr (RECOMP) {
-                __builtin_nontemporal_store(pack(left), &Ck[((size_t)sg * 2 + 0) * kBandRows + lane]);
-                __builtin_nontemporal_store(pack(diag), &Ck[((size_t)sg * 2 + 1) * kBandRows + lane]);
+                __builtin_nontemporal_store(left, &Ck[((size_t)sg * 2 + 0) * kBandRows + lane]);
+                __builtin_nontemporal_store(diag, &Ck[((size_t)sg * 2 + 1) * kBandRows + lane]);
             }
             auto steps = [&](auto capture) {
 #pragma unroll
                 for (int u = 0; u < kBlk; ++u) {
-                    if (kGet && CH != 1 && u == kPeekStep) cour.peek(p, sg + 1, lane);
-                    const Cell<SC> up = cell_shr1(left, kBatchTop ? tv[u] : (u == 0 ? top0[0] : top1[u - 1]));  // R[i-1][j]; lane 0 takes the row above the band
-                    Cell<SC> cur = dp_cell<SC>(diag, up, left, dcv[u], c2d);
-                    if (renorm_after(u)) renorm(cur);
-                    const uint64_t bits = pack(cur);
+                    // ask for the next macro-step's row above about one memory round trip before it
+                    // is needed: asked earlier, the answer would be "not written yet" too often
+                    if (u == kPeekStep && has_above) nxt_bits = peek_boundary(brow_in, jn, need_n);
+                    const double up = lane_shr1(left, u == 0 ? top0[0] : top1[u - 1]);  // R[i-1][j]; lane 0 takes the row above the band
+                    const float dc = dcv[u];
+                    double m;
+                    float L;
+                    softmin3_parts(diag, up, left, m, L);
+                    // every addition that builds the table is float64: a float32 rounding here would
+                    // differ between the two sweeps and add up along the alignment path
+                    const double cur = fma((double)dc, c2d, m) - (double)L;
                     if constexpr (!RECOMP)  // streamed once: keep it out of the caches
-                        __builtin_nontemporal_store(bits, &Rs[u * kBandRows + lane]);
-                    if constexpr (decltype(capture)::value) fin = (sg * kBlk + u == s_fin) ? bits : fin;
-                    my_eo[u] = bits;  // lane 63: value of column 32*sg + u - 63 for the band below
+                        __builtin_nontemporal_store(cur, &Rs[u * kBandRows + lane]);
+                    if constexpr (decltype(capture)::value) fin = (sg * kBlk + u == s_fin) ? cur : fin;
+                    my_eo[u] = cur;  // lane 63: value of column 32*sg + u - 63 for the band below
                     diag = up;
                     left = cur;
                 }
@@ -1170,39 +1011,39 @@ __device__ __forceinline__ void forward_dp_body(const Params &p, float *__restri
                 steps(std::true_type{});
             else
                 steps(std::false_type{});
+            // last row of the band: lanes 32..63 publish columns 32*sg - 63 + (lane - 32)
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            // the band's last row, for the band below (also from a chained pair's upper band: alignment_kernel reads it)
-            cour.publish(p, CH == 0 ? hand + (sg & 3) * kBlk : eo, sg, lane);
-            if (kGet && CH != 1) cour.deliver(p, sh.edge_in[slot][kGet ? 0 : (sg + 1) & 1], sg + 1, lane);
+            if (emit_bottom && lane >= kBlk) {
+                const int j = sg * kBlk + lane - kBlk - (kBandRows - 1);
+                // (a chained pair's upper band hands the row over through LDS; it still leaves it in
+                // memory, where alignment_kernel looks for the columns that can hold a non-zero E)
+                const double *src = (CH == 0) ? hand + (sg & 3) * kBlk : eo;
+                if (j >= 0 && j < M) publish_boundary(brow_out, j, src[lane - kBlk]);
+            }
+            if constexpr (CH != 1) {
+                double tn = kBig;
+                if (has_above) tn = resolve_boundary(p, brow_in, jn, need_n, lane, gave_up, nxt_bits);
+                if (lane < kBlk) top[lane] = tn;
+            }
         }
         __syncthreads();
     }
 
     // R[N,M] of the pair: cell (N-1, M-1) was stored at step M-1+lane by the lane that owns row N-1
     if (live && row0 + lane == Nl - 1) {
-        Cell<SC> r = unpack<SC>(RECOMP ? fin : Rk[(size_t)(Ml - 1 + lane) * kBandRows + lane]);
-        renorm(r);
-        p.rfinal[b] = pack(r);               // for the kernels that form E
-        value[b] = (float)(SC ? cell_log2(r) / (double)p.c2f : cell_log2(r) * p.inv_c2d);  // the paper's units
+        const double r = RECOMP ? fin : Rk[(size_t)(Ml - 1 + lane) * kBandRows + lane];
+        p.rfinal[b] = r;                     // table units, for the backward sweep
+        value[b] = (float)(r * p.inv_c2d);   // the paper's units
     }
     };
-    auto consume_as = [&](auto scaled_c) {
-        if constexpr (SLOTS == 2) {
-            if (slot == 0)
-                consume(std::integral_constant<int, 0>{}, scaled_c);
-            else
-                consume(std::integral_constant<int, 1>{}, scaled_c);
-        } else {
-            consume(std::integral_constant<int, -1>{}, scaled_c);
-        }
-    };
-    if constexpr (may_scale(KCH, SLOTS)) {
-        if (scaled) {
-            consume_as(std::true_type{});
-            return;
-        }
+    if constexpr (SLOTS == 2) {
+        if (slot == 0)
+            consume(std::integral_constant<int, 0>{});
+        else
+            consume(std::integral_constant<int, 1>{});
+    } else {
+        consume(std::integral_constant<int, -1>{});
     }
-    consume_as(std::false_type{});
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1517,7 +1358,7 @@ __device__ __forceinline__ void grad_E_block_any(const Params &p, const SweepRan
 
 template <int KCH, int SLOTS, int NPROD, bool GRAD = false>
 __device__ __forceinline__ void reverse_dp_body(const Params &p, WgShared<SLOTS> &sh, unsigned &ticket_s,
-                                                uint64_t (&edge_out)[SLOTS][kEdgeOut], uint64_t (&hand)[kHandDoubles])
+                                                double (&edge_out)[SLOTS][kEdgeOut], double (&hand)[kHandDoubles])
 {
     static_assert(SLOTS == 4 || SLOTS == 2 || SLOTS == 1, "supported workgroup shapes");
     static_assert(NPROD == 1 || (NPROD == 2 && KCH > 0), "two producers only split MFMA work");
@@ -1533,13 +1374,12 @@ __device__ __forceinline__ void reverse_dp_body(const Params &p, WgShared<SLOTS>
     }
 
     if (threadIdx.x == 0) ticket_s = atomicAdd(&p.hdr->bwd_ticket, 1u);
-    if constexpr (may_scale(KCH, SLOTS)) find_cost_maximum<kThreads>(p, sh.wave_max);
     for (int e = threadIdx.x; e < SLOTS * kRingFloats; e += kThreads) (&sh.ring[0][0])[e] = kBigCost;
     int producer, slot;  // producer: 0 = consumer, 1.. = producer number
     if constexpr (SLOTS == 4) {
         elect_role(sh, lane, w, 1 + NPROD, producer, slot);
     } else if constexpr (SLOTS == 2) {
-        for (int e = threadIdx.x; e < kHandDoubles; e += kThreads) hand[e] = kBigBits;
+        for (int e = threadIdx.x; e < kHandDoubles; e += kThreads) hand[e] = kBig;
         chain_role(w, producer, slot);
         __syncthreads();
     } else {
@@ -1572,9 +1412,6 @@ __device__ __forceinline__ void reverse_dp_body(const Params &p, WgShared<SLOTS>
         rg = sweep_range(p, (p.nbands - 1 - kk) * kBandRows, (p.nbands - 1 - kk) * kBandRows, nl, ml);
     }
     const int k = p.nbands - 1 - kk;
-    bool scaled = false;
-    if constexpr (may_scale(KCH, SLOTS)) scaled = use_scaled<kThreads>(p, sh.wave_max);
-    const float cs = scaled ? p.c2f : 1.0f;
     const bool live = (kk < p.nbands) && (b < p.B) && rg.hi >= rg.lo;
     const int lag = (SLOTS == 2) ? kChainLag * slot : 0;
     const int niter = max(rg.hi - rg.lo + 1, 0) + ((SLOTS == 2) ? kChainLag : 0);
@@ -1612,18 +1449,6 @@ __device__ __forceinline__ void reverse_dp_body(const Params &p, WgShared<SLOTS>
     static_assert(!GRAD || dp_recompute(KCH, SLOTS), "the contracting sweep is the recomputing one");
     constexpr bool kProducerFlush = !GRAD && !TSWEEP && !(dp_recompute(KCH, SLOTS) && KCH > 4);
 
-    // chained pair (slot 0: the lower band): its first row reaches slot 1 through LDS, and memory besides
-    const bool row_from_lds = SLOTS == 2 && slot == 1;
-    constexpr bool kGet = consumer_fetches(KCH, SLOTS);
-
-    Courier<-1> cour;
-    {
-        const int kc = live ? k : 0;
-        cour.has_in = live && k + 1 < p.nbands && !row_from_lds;
-        cour.emit = live && k > 0;
-        cour.in = p.brow_b + ((size_t)bb * p.nbands + (cour.has_in ? kc + 1 : kc)) * M;
-        cour.out = p.brow_b + ((size_t)bb * p.nbands + kc) * M;
-    }
     if (producer) {
         // Besides the cost blocks, the producers write out the E blocks the consumer finished in the
         // previous macro-step `done`: (upper rows, done) and (lower rows, done-1).  Each producer
@@ -1635,96 +1460,100 @@ __device__ __forceinline__ void reverse_dp_body(const Params &p, WgShared<SLOTS>
                 if (lower) flush_E_block(p, rg, ring, Eb, nzb, 1, done - 1, row0, lane, dead, 0, idxb);
             }
         };
-        // (as in the forward sweep; upper, lower: the block rows whose finished E blocks this wavefront writes out)
-        auto produce = [&](bool courier, bool upper, bool lower, auto &&start, auto &&work) {
-            if (live) {
-                if (!kGet && courier) {
-                    (&sh.edge_in[slot][0][0])[lane] = kBigBits;
-                    cour.peek(p, sg0, lane);
+        // blocks the first macro-step reads: (upper rows, sg0-1), (lower rows, sg0-1), (lower rows, sg0-2)
+        if constexpr (KCH > 0 && NPROD == 2) {
+            // producer 1 makes (upper rows, sg-2), producer 2 makes (lower rows, sg-3)
+            auto body = [&](auto &mp, bool upper) {
+                if (live) {
+                    mp.init(pl, xh, xnb, xisb, rowtab, row0, lane);
+                    if (upper) {
+                        mp.block_now(pl, yh, ynb, yisb, ring, rowtab, 0, sg0 - 1, row0, lane);
+                    } else {
+                        mp.block_now(pl, yh, ynb, yisb, ring, rowtab, 1, sg0 - 1, row0, lane);
+                        mp.block_now(pl, yh, ynb, yisb, ring, rowtab, 1, sg0 - 2, row0, lane);
+                    }
+                    mp.prime(pl, yh, ynb, yisb, sg0, lane);
                 }
-                start();
-                if (!kGet && courier) cour.deliver(p, sh.edge_in[slot][kGet ? 0 : sg0 & 1], sg0, lane);
+                __syncthreads();
+                for (int it = 0; it < niter; ++it) {
+                    const int sg = sg0 - (it - lag);
+                    if (live && sg >= rg.lo && sg <= sg0) {
+                        if (sg < sg0) flush(sg + 1, upper, !upper);
+                        mp.run(pl, yh, ynb, yisb, ring, rowtab, sg, row0, lane);
+                    }
+                    __syncthreads();
+                }
+                if (live) flush(rg.lo, upper, !upper);
+            };
+            if (producer == 1) {
+                HalfProducer<KCH, -1, 0, 1> mp;
+                body(mp, true);
+            } else {
+                HalfProducer<KCH, -1, 1, 1> mp;
+                body(mp, false);
+            }
+        } else if constexpr (KCH > 0) {
+            HalfProducer<KCH, -1, 0, 2> mp;
+            if (live) {
+                mp.init(pl, xh, xnb, xisb, rowtab, row0, lane);
+                mp.block_now(pl, yh, ynb, yisb, ring, rowtab, 0, sg0 - 1, row0, lane);
+                mp.block_now(pl, yh, ynb, yisb, ring, rowtab, 1, sg0 - 1, row0, lane);
+                mp.block_now(pl, yh, ynb, yisb, ring, rowtab, 1, sg0 - 2, row0, lane);
+                mp.prime(pl, yh, ynb, yisb, sg0, lane);
             }
             __syncthreads();
             for (int it = 0; it < niter; ++it) {
                 const int sg = sg0 - (it - lag);
-                                if (live && sg >= rg.lo && sg <= sg0) {
-                    if (sg < sg0) flush(sg + 1, upper, lower);
-                    work(sg, [&] { if (!kGet && courier) cour.peek(p, sg - 1, lane); });
-                    if (!kGet && courier) cour.deliver(p, sh.edge_in[slot][kGet ? 0 : (sg - 1) & 1], sg - 1, lane);
+                if (live && sg >= rg.lo && sg <= sg0) {
+                    if (sg < sg0) flush(sg + 1, true, true);
+                    mp.run(pl, yh, ynb, yisb, ring, rowtab, sg, row0, lane);
                 }
                 __syncthreads();
             }
-            if (live) flush(rg.lo, upper, lower);
-        };
-        // blocks the first macro-step reads: (upper rows, sg0-1), (lower rows, sg0-1), (lower rows, sg0-2)
-        if constexpr (KCH > 0 && NPROD == 2) {
-            // producer 1 makes (upper rows, sg-2), producer 2 makes (lower rows, sg-3)
-            if (producer == 1) {
-                HalfProducer<KCH, -1, 0, 1> mp;
-                produce(true, true, false,
-                        [&] {
-                            mp.init(pl, xh, xnb, xisb, rowtab, row0, lane, cs);
-                            mp.block_now(pl, yh, ynb, yisb, ring, rowtab, 0, sg0 - 1, row0, lane);
-                            mp.prime(pl, yh, ynb, yisb, sg0, lane);
-                        },
-                        [&](int sg, auto &&late) { mp.run(pl, yh, ynb, yisb, ring, rowtab, sg, row0, lane, late); });
-            } else {
-                HalfProducer<KCH, -1, 1, 1> mp;
-                produce(false, false, true,
-                        [&] {
-                            mp.init(pl, xh, xnb, xisb, rowtab, row0, lane, cs);
-                            mp.block_now(pl, yh, ynb, yisb, ring, rowtab, 1, sg0 - 1, row0, lane);
-                            mp.block_now(pl, yh, ynb, yisb, ring, rowtab, 1, sg0 - 2, row0, lane);
-                            mp.prime(pl, yh, ynb, yisb, sg0, lane);
-                        },
-                        [&](int sg, auto &&late) { mp.run(pl, yh, ynb, yisb, ring, rowtab, sg, row0, lane, late); });
-            }
-        } else if constexpr (KCH > 0) {
-            HalfProducer<KCH, -1, 0, 2> mp;
-            produce(true, true, true,
-                    [&] {
-                        mp.init(pl, xh, xnb, xisb, rowtab, row0, lane, cs);
-                        mp.block_now(pl, yh, ynb, yisb, ring, rowtab, 0, sg0 - 1, row0, lane);
-                        mp.block_now(pl, yh, ynb, yisb, ring, rowtab, 1, sg0 - 1, row0, lane);
-                        mp.block_now(pl, yh, ynb, yisb, ring, rowtab, 1, sg0 - 2, row0, lane);
-                        mp.prime(pl, yh, ynb, yisb, sg0, lane);
-                    },
-                    [&](int sg, auto &&late) { mp.run(pl, yh, ynb, yisb, ring, rowtab, sg, row0, lane, late); });
+            if (live) flush(rg.lo, true, true);
         } else if constexpr (KCH == 0) {
-            produce(true, true, true,
-                    [&] {
-                        generic_block(pl, b, ring, 0, sg0 - 1, row0, lane, cs);
-                        generic_block(pl, b, ring, 1, sg0 - 1, row0, lane, cs);
-                        generic_block(pl, b, ring, 1, sg0 - 2, row0, lane, cs);
-                    },
-                    [&](int sg, auto &&late) {
-                        generic_block(pl, b, ring, 0, sg - 2, row0, lane, cs);
-                        generic_block(pl, b, ring, 1, sg - 3, row0, lane, cs);
-                        late();
-                    });
+            if (live) {
+                generic_block(pl, b, ring, 0, sg0 - 1, row0, lane);
+                generic_block(pl, b, ring, 1, sg0 - 1, row0, lane);
+                generic_block(pl, b, ring, 1, sg0 - 2, row0, lane);
+            }
+            __syncthreads();
+            for (int it = 0; it < niter; ++it) {
+                const int sg = sg0 - (it - lag);
+                if (live && sg >= rg.lo && sg <= sg0) {
+                    if (sg < sg0) flush(sg + 1, true, true);
+                    generic_block(pl, b, ring, 0, sg - 2, row0, lane);
+                    generic_block(pl, b, ring, 1, sg - 3, row0, lane);
+                }
+                __syncthreads();
+            }
+            if (live) flush(rg.lo, true, true);
         } else {
             const float *cost_b = p.cost + (size_t)bb * N * M;
             float4 pre[2][4];
-            auto load = [&](float4 (&v)[4], int rb, int cb) { load_cost_block(v, cost_b, rb, cb, row0, Nl, Ml, M, p.window, p.vec_m != 0, lane); };
-            produce(true, true, true,
-                    [&] {
-                        load(pre[0], 0, sg0 - 1);
-                        store_cost_block(ring, pre[0], 0, sg0 - 1, lane, cs);
-                        load(pre[0], 1, sg0 - 1);
-                        store_cost_block(ring, pre[0], 1, sg0 - 1, lane, cs);
-                        load(pre[0], 1, sg0 - 2);
-                        store_cost_block(ring, pre[0], 1, sg0 - 2, lane, cs);
-                        load(pre[0], 0, sg0 - 2);
-                        load(pre[1], 1, sg0 - 3);
-                    },
-                    [&](int sg, auto &&late) {
-                        store_cost_block(ring, pre[0], 0, sg - 2, lane, cs);
-                        store_cost_block(ring, pre[1], 1, sg - 3, lane, cs);
-                        late();
-                        load(pre[0], 0, sg - 3);
-                        load(pre[1], 1, sg - 4);
-                    });
+            if (live) {
+                load_cost_block(pre[0], cost_b, 0, sg0 - 1, row0, Nl, Ml, M, p.window, p.vec_m != 0, lane);
+                store_cost_block(ring, pre[0], 0, sg0 - 1, lane);
+                load_cost_block(pre[0], cost_b, 1, sg0 - 1, row0, Nl, Ml, M, p.window, p.vec_m != 0, lane);
+                store_cost_block(ring, pre[0], 1, sg0 - 1, lane);
+                load_cost_block(pre[0], cost_b, 1, sg0 - 2, row0, Nl, Ml, M, p.window, p.vec_m != 0, lane);
+                store_cost_block(ring, pre[0], 1, sg0 - 2, lane);
+                load_cost_block(pre[0], cost_b, 0, sg0 - 2, row0, Nl, Ml, M, p.window, p.vec_m != 0, lane);
+                load_cost_block(pre[1], cost_b, 1, sg0 - 3, row0, Nl, Ml, M, p.window, p.vec_m != 0, lane);
+            }
+            __syncthreads();
+            for (int it = 0; it < niter; ++it) {
+                const int sg = sg0 - (it - lag);
+                if (live && sg >= rg.lo && sg <= sg0) {
+                    if (sg < sg0) flush(sg + 1, true, true);
+                    store_cost_block(ring, pre[0], 0, sg - 2, lane);
+                    store_cost_block(ring, pre[1], 1, sg - 3, lane);
+                    load_cost_block(pre[0], cost_b, 0, sg - 3, row0, Nl, Ml, M, p.window, p.vec_m != 0, lane);
+                    load_cost_block(pre[1], cost_b, 1, sg - 4, row0, Nl, Ml, M, p.window, p.vec_m != 0, lane);
+                }
+                __syncthreads();
+            }
+            if (live) flush(rg.lo, true, true);
         }
         return;
     }
@@ -1736,42 +1565,42 @@ __device__ __forceinline__ void reverse_dp_body(const Params &p, WgShared<SLOTS>
     // CH: -1 = both neighbouring bands are reached through memory; 0 = the band above is the other
     // band of this workgroup (this band's first row goes to the LDS hand-over ring); 1 = the band
     // below is.
-    auto consume = [&](auto chain_c, auto scaled_c) {
+    auto consume = [&](auto chain_c) {
     constexpr int CH = decltype(chain_c)::value;
-    constexpr bool SC = decltype(scaled_c)::value;
     const double c2d = p.c2d;  // log2(e)/gamma
-    Cell<SC> right = cell_none<SC>();  // T[i][j+1]
-    Cell<SC> diag = cell_none<SC>();   // T[i+1][j+1]
+    bool gave_up = false;
+    double right = kBig;  // T[i][j+1]
+    double diag = kBig;   // T[i+1][j+1]
     // step at which this lane meets the cell whose diagonal successor is T[N+1,M+1] = 0, and the
     // macro-step in which that happens in this band
     const int s_corner = (live && row0 + lane == Nl - 1) ? (Ml - 1 + lane) : -1;
     const int t_last = Nl - 1 - row0;
     const int sg_corner = (live && t_last >= 0 && t_last < kBandRows) ? (Ml - 1 + t_last) / kBlk : -1;
-    [[maybe_unused]] Cell<SC> fin = cell_origin<SC>();
-    if constexpr (!TSWEEP) {
-        if (live) fin = unpack<SC>(p.rfinal[b]);
-    }
-    [[maybe_unused]] float fin_inv = 1.0f;  // (mantissas of rfinal are normalised: this is in (1, 2])
-    if constexpr (SC) fin_inv = 1.0f / fin.m;
+    const double Rfin = (live && !TSWEEP) ? p.rfinal[b] : 0.0;
     const int kc = live ? k : 0;
+    const bool has_below = live && (k + 1 < p.nbands) && CH != 1;  // through memory
+    const bool emit_top = live && k > 0;                           // the band's first row goes to memory
     constexpr bool RECOMP = dp_recompute(KCH, SLOTS);
     static_assert(RECOMP != TSWEEP, "a reverse sweep either stores its own table or recomputes R and forms E");
+    const unsigned long long *brow_in = p.brow_b + ((size_t)bb * p.nbands + (has_below ? kc + 1 : kc)) * M;
+    unsigned long long *brow_out = p.brow_b + ((size_t)bb * p.nbands + kc) * M;
     // (table pointers are those of the band's macro-step 0; the table starts at macro-step table_base)
     const ptrdiff_t tb = table_base(p, kc);
     const ptrdiff_t band_off = (((ptrdiff_t)bb * p.nbands + kc) * (ptrdiff_t)p.nm_tab - tb) * kBlk * kBandRows;
-    uint64_t *Qk = TSWEEP ? p.Q + band_off : nullptr;
-    const uint64_t *Ck = RECOMP ? p.ckpt + (((ptrdiff_t)bb * p.nbands + kc) * (ptrdiff_t)p.nm_tab - tb) * 2 * kBandRows : nullptr;
+    double *Qk = TSWEEP ? p.Q + band_off : nullptr;
+    const double *Ck = RECOMP ? p.ckpt + (((ptrdiff_t)bb * p.nbands + kc) * (ptrdiff_t)p.nm_tab - tb) * 2 * kBandRows : nullptr;
     // the forward's row above this band (final values, written by the forward call)
-    const uint64_t *ftop_g = reinterpret_cast<const uint64_t *>(p.brow) + ((size_t)bb * p.nbands + (kc > 0 ? kc - 1 : 0)) * M;
-    uint64_t *ftop = sh.ftop[slot];
+    const double *ftop_g = reinterpret_cast<const double *>(p.brow) + ((size_t)bb * p.nbands + (kc > 0 ? kc - 1 : 0)) * M;
+    double *ftop = sh.ftop[slot];
     float *my_ring = ring + lane * kRingStride;
-    uint64_t *eo = edge_out[slot];
+    double *bot = sh.edge_in[slot];
+    double *eo = edge_out[slot];
 
     bool dead_prev = true;  // the macro-step before the first one: beyond the table, nothing there
-    // RECOMP: R of the macro-step, relative to R[N,M]: the float64 difference, or (mantissa / R[N,M]'s, scale difference)
-    Cell<SC> Rq[RECOMP ? kBlk : 1];
-    uint64_t ck_left = kBigBits, ck_diag = kBigBits;  // RECOMP: forward lane state at the start of the coming macro-step
-    uint64_t ftop_next = kBigBits;                    // RECOMP: forward's row above the band for the coming macro-step
+    // R of the first macro-step; afterwards each value is reloaded one macro-step ahead, right after use
+    double Rq[kBlk];
+    double ck_left = kBig, ck_diag = kBig;  // RECOMP: forward lane state at the start of the coming macro-step
+    double ftop_next = kBig;                // RECOMP: forward's row above the band for the coming macro-step
     if constexpr (RECOMP) {
         if (live) {
             ck_left = Ck[((size_t)sg0 * 2 + 0) * kBandRows + lane];
@@ -1780,30 +1609,38 @@ __device__ __forceinline__ void reverse_dp_body(const Params &p, WgShared<SLOTS>
             if (k > 0 && lane < kBlk && jf < M) ftop_next = ftop_g[jf];
         }
     }
-    if (kGet && CH != 1 && live) {
-        (&sh.edge_in[slot][0][0])[lane] = kBigBits;
-        cour.peek(p, sg0, lane);
-        cour.deliver(p, sh.edge_in[slot][kGet ? 0 : sg0 & 1], sg0, lane);
-    }
 
+    // row below the band for the first macro-step: lane l >= 32 brings column 32*sg - 63 + (l - 32),
+    // which lane 63 meets at step u = l - 32
+    if constexpr (CH != 1) {
+        double b0 = kBig;
+        if (has_below) {
+            const int jj = sg0 * kBlk + lane - kBlk - (kBandRows - 1);
+            const bool need = lane >= kBlk && jj >= 0 && jj < M;
+            b0 = resolve_boundary(p, brow_in, jj, need, lane, gave_up, peek_boundary(brow_in, jj, need));
+        }
+        if (lane >= kBlk) bot[lane - kBlk] = b0;
+    }
     __syncthreads();
 
     for (int it = 0; it < niter; ++it) {
         const int sg = sg0 - (it - lag);
         if (live && sg >= rg.lo && sg <= sg0) {
+            unsigned long long nxt_bits = (unsigned long long)__double_as_longlong(kBig);
+            const int jn = (sg - 1) * kBlk + lane - kBlk - (kBandRows - 1);
+            const bool need_n = has_below && lane >= kBlk && jn >= 0 && jn < M;
             float *rd = my_ring + (sg & 3) * kBlk;
             // The row below, column 32*sg + u - 63 at step u: from the incoming boundary values, or
             // from the hand-over ring, where the band below put column c at slot c mod 128.
-            const uint64_t *bot = sh.edge_in[slot][kGet ? 0 : sg & 1];
-            const uint64_t *bot31 = bot + (kBlk - 1), *bot0 = bot;  // step 31, steps 0..30
+            const double *bot31 = bot + (kBlk - 1), *bot0 = bot;  // step 31, steps 0..30
             if constexpr (CH == 1) {
                 bot31 = hand + ((sg - 1) & 3) * kBlk;
                 bot0 = hand + ((sg - 2) & 3) * kBlk + 1;
             }
             // lane 0's values are the band's first row (column 32*sg + u at step u)
-            uint64_t *my_eo = eo + ((lane == 0) ? 0 : kBlk + lane);
+            double *my_eo = eo + ((lane == 0) ? 0 : kBlk + lane);
             if constexpr (CH == 0) my_eo = hand + ((lane == 0) ? (sg & 3) * kBlk : kHandRing + lane);
-            uint64_t *Qs = TSWEEP ? Qk + (size_t)sg * kBlk * kBandRows : nullptr;
+            double *Qs = TSWEEP ? Qk + (size_t)sg * kBlk * kBandRows : nullptr;
             const int sbase = sg * kBlk;
             // Can any cell of this macro-step have a non-zero E (in float32)?  Every R of the macro-step
             // is at least the smallest value entering it (the lanes' forward state at its start, the
@@ -1812,49 +1649,39 @@ __device__ __forceinline__ void reverse_dp_body(const Params &p, WgShared<SLOTS>
             // the row below).  If R[N,M] - min R - min Q is far below the smallest float32 exponent,
             // E is zero throughout: the macro-step only continues T (no recomputation, no exp2).
             bool dead = false;
-            if constexpr (RECOMP && SC) {
-                // (an entry's value is at least its scale minus 52, see the range of mantissas at Cell)
-                int rmin = min(unpack<true>(ck_left).r, unpack<true>(ck_diag).r), qmin = min(right.r, diag.r);
+            if constexpr (RECOMP) {
+                float rmin = (float)min_f64(ck_left, ck_diag), qmin = (float)min_f64(right, diag);
                 if (lane < kBlk) {
-                    rmin = min(rmin, unpack<true>(ftop_next).r);
-                    qmin = min(qmin, unpack<true>(bot[lane]).r);
-                }
-                // 157 (float32), 2 x 32 log2(3) = 102, 2 x 52
-                dead = sat_sub(sat_add(wave_min_i32(rmin), wave_min_i32(qmin)), fin.r) > 380 && sg != sg_corner;
-                dead = __builtin_amdgcn_readfirstlane((int)dead) != 0;
-            } else if constexpr (RECOMP) {
-                float rmin = (float)min_f64(unpack<false>(ck_left).v, unpack<false>(ck_diag).v), qmin = (float)min_f64(right.v, diag.v);
-                if (lane < kBlk) {
-                    rmin = fminf(rmin, (float)unpack<false>(ftop_next).v);
-                    qmin = fminf(qmin, (float)unpack<false>(bot[lane]).v);
+                    rmin = fminf(rmin, (float)ftop_next);
+                    qmin = fminf(qmin, (float)bot[lane]);
                 }
                 rmin = wave_min_f32(rmin);
                 qmin = wave_min_f32(qmin);
                 // 157 (float32), 2 x 32 log2(3) = 102, rounding of the two minima to float32 (<= 2 x 16)
-                dead = __builtin_amdgcn_readfirstlane((int)(((double)rmin + (double)qmin > fin.v + 300.0) && sg != sg_corner)) != 0;
+                dead = __builtin_amdgcn_readfirstlane((int)(((double)rmin + (double)qmin > Rfin + 300.0) && sg != sg_corner)) != 0;
             }
             if constexpr (RECOMP) {
                 // recompute R of this macro-step from the forward's checkpoint (same arithmetic, same
                 // cost values, hence the same bits the forward had)
-                Cell<SC> fl = unpack<SC>(ck_left), fd = unpack<SC>(ck_diag);
+                double fl = ck_left, fd = ck_diag;
                 if (lane < kBlk) ftop[lane] = ftop_next;
                 if (sg > rg.lo) {  // everything the next macro-step's recomputation needs, one macro-step ahead
                     ck_left = __builtin_nontemporal_load(&Ck[((size_t)(sg - 1) * 2 + 0) * kBandRows + lane]);
                     ck_diag = __builtin_nontemporal_load(&Ck[((size_t)(sg - 1) * 2 + 1) * kBandRows + lane]);
                     const int jf = sbase - kBlk + lane;
-                    ftop_next = kBigBits;
+                    ftop_next = kBig;
                     if (k > 0 && lane < kBlk && jf < M) ftop_next = __builtin_nontemporal_load(&ftop_g[jf]);
                 }
                 if (!dead) {
 #pragma unroll
                     for (int u = 0; u < kBlk; ++u) {
-                        const Cell<SC> up = cell_shr1(fl, ftop[u]);
-                        Cell<SC> cur = dp_cell<SC>(fd, up, fl, rd[u], c2d);
-                        if (renorm_after(u)) renorm(cur);
-                        if constexpr (SC)
-                            Rq[u] = {cur.m * fin_inv, sat_sub(fin.r, cur.r)};
-                        else
-                            Rq[u] = {fin.v - cur.v};
+                        const double up = lane_shr1(fl, ftop[u]);
+                        const float dcf = rd[u];
+                        double mf;
+                        float Lf;
+                        softmin3_parts(fd, up, fl, mf, Lf);
+                        const double cur = fma((double)dcf, c2d, mf) - (double)Lf;
+                        Rq[u] = Rfin - cur;
                         fd = up;
                         fl = cur;
                     }
@@ -1862,58 +1689,40 @@ __device__ __forceinline__ void reverse_dp_body(const Params &p, WgShared<SLOTS>
             }
             // (small problems: the macro-step's 32 cost values in one batch, as in the forward sweep)
             [[maybe_unused]] float dcv[TSWEEP ? kBlk : 1];
-            [[maybe_unused]] uint64_t bv[TSWEEP ? kBlk : 1];
             if constexpr (TSWEEP) {
 #pragma unroll
-                for (int u = kBlk - 1; u >= 0; --u) {
-                    dcv[u] = rd[u];
-                    if constexpr (SC) bv[u] = u == kBlk - 1 ? bot31[0] : bot0[u];
-                }
-                if constexpr (SC) __builtin_amdgcn_sched_barrier(0);
+                for (int u = 0; u < kBlk; ++u) dcv[u] = rd[u];
             }
             auto steps = [&](auto corner, auto alive) {
 #pragma unroll
             for (int u = kBlk - 1; u >= 0; --u) {
-                if (kGet && CH != 1 && u == kBlk - 1 - kPeekStep) cour.peek(p, sg - 1, lane);
-                uint64_t below;
-                if constexpr (TSWEEP && SC)
-                    below = bv[u];
-                else
-                    below = u == kBlk - 1 ? bot31[0] : bot0[u];
-                const Cell<SC> down = cell_shl1(right, below);  // T[i+1][j]; lane 63 takes the row below the band
+                if (u == kBlk - 1 - kPeekStep && has_below) nxt_bits = peek_boundary(brow_in, jn, need_n);
+                const double down = lane_shl1(right, u == kBlk - 1 ? bot31[0] : bot0[u]);  // T[i+1][j]; lane 63 takes the row below the band
                 float dc;
                 if constexpr (TSWEEP)
                     dc = dcv[u];
                 else
                     dc = rd[u];
-                Cell<SC> dg = diag;
-                if constexpr (decltype(corner)::value) {
-                    if (sbase + u == s_corner) dg = cell_origin<SC>();
-                }
-                const Soft<SC> q = soft3<SC>(dg, down, right);
-                Cell<SC> cur;
-                if constexpr (TSWEEP && !SC) {
+                const double dg = (decltype(corner)::value && sbase + u == s_corner) ? 0.0 : diag;
+                double m;
+                float L;
+                softmin3_parts(dg, down, right, m, L);
+                double cur;
+                if constexpr (TSWEEP) {
                     // the soft-minimum part Q = T - d goes to the table: log2 E = R[N,M] - R[i,j] - Q[i,j]
-                    const double qv = q.m - (double)q.L;
-                    __builtin_nontemporal_store((uint64_t)__double_as_longlong(qv), &Qs[u * kBandRows + lane]);
-                    cur = {fma((double)dc, c2d, qv)};
-                } else if constexpr (TSWEEP) {
-                    __builtin_nontemporal_store(pack(Cell<true>{q.s, q.r}), &Qs[u * kBandRows + lane]);
-                    cur = add_cost<SC>(q, dc, c2d);
+                    const double q = m - (double)L;
+                    __builtin_nontemporal_store(q, &Qs[u * kBandRows + lane]);
+                    cur = fma((double)dc, c2d, q);
                 } else {
-                    cur = add_cost<SC>(q, dc, c2d);
+                    cur = fma((double)dc, c2d, m) - (double)L;
                     if constexpr (decltype(alive)::value) {
                         // log2 E = R[N,M] - R[i,j] - (m - L) in table units
-                        if constexpr (SC)
-                            rd[u] = __builtin_amdgcn_ldexpf(Rq[u].m * q.s, sat_sub(Rq[u].r, q.r));
-                        else
-                            rd[u] = __builtin_amdgcn_exp2f((float)(Rq[u].v - q.m) + q.L);
+                        rd[u] = __builtin_amdgcn_exp2f((float)(Rq[u] - m) + L);
                     } else {
                         rd[u] = 0.0f;
                     }
                 }
-                if (renorm_after(u)) renorm(cur);
-                my_eo[u] = pack(cur);  // lane 0: value of column 32*sg + u for the band above
+                my_eo[u] = cur;  // lane 0: value of column 32*sg + u for the band above
                 diag = down;
                 right = cur;
             }
@@ -1925,9 +1734,13 @@ __device__ __forceinline__ void reverse_dp_body(const Params &p, WgShared<SLOTS>
             else
                 steps(std::false_type{}, std::true_type{});
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            // the band's first row, for the band above
-            cour.publish(p, CH == 0 ? hand + (sg & 3) * kBlk : eo, sg, lane);
-            if (kGet && CH != 1) cour.deliver(p, sh.edge_in[slot][kGet ? 0 : (sg - 1) & 1], sg - 1, lane);
+            // first row of the band, columns 32*sg .. 32*sg+31, for the band above
+            if (emit_top && lane < kBlk) {
+                const int j = sg * kBlk + lane;
+                // (also from a chained pair's lower band, whose first row travels through LDS: see the forward sweep)
+                const double *src = (CH == 0) ? hand + (sg & 3) * kBlk : eo;
+                if (j < M) publish_boundary(brow_out, j, src[lane]);
+            }
             // the E blocks this macro-step completed, (upper rows, sg) and (lower rows, sg-1): written
             // out by the producers during the next macro-step, or here
             // (both hold cells of this macro-step and the one before it only)
@@ -1947,27 +1760,23 @@ __device__ __forceinline__ void reverse_dp_body(const Params &p, WgShared<SLOTS>
             } else if constexpr (!TSWEEP) {
                 if (lane == 0) sh.blk_dead[slot][sg & 1] = blocks_dead ? 1 : 0;
             }
+            if constexpr (CH != 1) {
+                double bn = kBig;
+                if (has_below) bn = resolve_boundary(p, brow_in, jn, need_n, lane, gave_up, nxt_bits);
+                if (lane >= kBlk) bot[lane - kBlk] = bn;
+            }
         }
         __syncthreads();
     }
     };
-    auto consume_as = [&](auto scaled_c) {
-        if constexpr (SLOTS == 2) {
-            if (slot == 0)
-                consume(std::integral_constant<int, 0>{}, scaled_c);
-            else
-                consume(std::integral_constant<int, 1>{}, scaled_c);
-        } else {
-            consume(std::integral_constant<int, -1>{}, scaled_c);
-        }
-    };
-    if constexpr (may_scale(KCH, SLOTS)) {
-        if (scaled) {
-            consume_as(std::true_type{});
-            return;
-        }
+    if constexpr (SLOTS == 2) {
+        if (slot == 0)
+            consume(std::integral_constant<int, 0>{});
+        else
+            consume(std::integral_constant<int, 1>{});
+    } else {
+        consume(std::integral_constant<int, -1>{});
     }
-    consume_as(std::false_type{});
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -2000,16 +1809,13 @@ constexpr int kAlignRingCols = 64, kAlignRingStride = 65;
 // whose entering term exceeds thr has E < M * 2^thr, which float32 cannot tell from 0, and likewise
 // right of the last column whose leaving term exceeds thr.  Returns that column range (the whole row
 // for the first band's left end and for the right end of the band that holds the pair's last row).
-template <bool SC>
-__device__ __forceinline__ void live_columns(const Params &p, int b, int k, int Nl, int Ml, uint64_t fin, int lane,
+__device__ __forceinline__ void live_columns(const Params &p, int b, int k, int Nl, int Ml, double Rfin, int lane,
                                              int &first, int &last)
 {
-    const double Rfin = cell_log2(unpack<SC>(fin));
     const double thr = -(157.0 + (double)(32 - __builtin_clz((unsigned)p.M)));
     auto row = [&](const unsigned long long *rows, int band, int j) {
-        return rows[((size_t)b * p.nbands + band) * p.M + j];
+        return __longlong_as_double((long long)rows[((size_t)b * p.nbands + band) * p.M + j]);
     };
-    auto val = [](uint64_t bits) { return cell_log2(unpack<SC>(bits)); };  // (no alignment: about 1e300, or infinite)
     // under a band constraint only the columns within the window of the band's rows can matter
     const int row0 = k * kBandRows;
     const int jlo = p.window < kNoWindow ? max(0, row0 - p.window - 1) : 0;
@@ -2020,19 +1826,19 @@ __device__ __forceinline__ void live_columns(const Params &p, int b, int k, int 
     if (k > 0) {
         int f = Ml;
         for (int j0 = jlo + lane; j0 <= jhi; j0 += kBandRows * kScan) {
-            uint64_t ra[kScan], rb[kScan], tq[kScan];
+            double ra[kScan], rb[kScan], tq[kScan];
 #pragma unroll
             for (int i = 0; i < kScan; ++i) {
                 const int j = j0 + i * kBandRows;
                 const bool in = j <= jhi;
-                ra[i] = in ? row(p.brow, k - 1, j) : kBigBits;
-                rb[i] = (in && j > 0) ? row(p.brow, k - 1, j - 1) : kBigBits;
-                tq[i] = in ? row(p.brow_b, k, j) : kBigBits;
+                ra[i] = in ? row(p.brow, k - 1, j) : kBig;
+                rb[i] = (in && j > 0) ? row(p.brow, k - 1, j - 1) : kBig;
+                tq[i] = in ? row(p.brow_b, k, j) : kBig;
             }
 #pragma unroll
             for (int i = 0; i < kScan; ++i) {
                 const int j = j0 + i * kBandRows;
-                const double term = (Rfin - val(tq[i])) - min_f64(val(ra[i]), val(rb[i])) + 1.0;
+                const double term = (Rfin - tq[i]) - min_f64(ra[i], rb[i]) + 1.0;
                 if (j <= jhi && term > thr) f = min(f, j);
             }
         }
@@ -2044,19 +1850,19 @@ __device__ __forceinline__ void live_columns(const Params &p, int b, int k, int 
     if (k != (Nl - 1) / kBandRows && k + 1 < p.nbands) {
         int l = -1;
         for (int j0 = jlo + lane; j0 <= jhi; j0 += kBandRows * kScan) {
-            uint64_t ta[kScan], tb[kScan], rq[kScan];
+            double ta[kScan], tb[kScan], rq[kScan];
 #pragma unroll
             for (int i = 0; i < kScan; ++i) {
                 const int j = j0 + i * kBandRows;
                 const bool in = j <= jhi;
-                ta[i] = in ? row(p.brow_b, k + 1, j) : kBigBits;
-                tb[i] = (in && j + 1 < Ml) ? row(p.brow_b, k + 1, j + 1) : kBigBits;
-                rq[i] = in ? row(p.brow, k, j) : kBigBits;
+                ta[i] = in ? row(p.brow_b, k + 1, j) : kBig;
+                tb[i] = (in && j + 1 < Ml) ? row(p.brow_b, k + 1, j + 1) : kBig;
+                rq[i] = in ? row(p.brow, k, j) : kBig;
             }
 #pragma unroll
             for (int i = 0; i < kScan; ++i) {
                 const int j = j0 + i * kBandRows;
-                const double term = (Rfin - val(rq[i])) - min_f64(val(ta[i]), val(tb[i])) + 1.0;
+                const double term = (Rfin - rq[i]) - min_f64(ta[i], tb[i]) + 1.0;
                 if (j <= jhi && term > thr) l = max(l, j);
             }
         }
@@ -2065,27 +1871,6 @@ __device__ __forceinline__ void live_columns(const Params &p, int b, int k, int 
         last = l;
     }
 }
-
-// log2 of E[i,j] from the two table entries, as E itself
-template <bool SC> struct Combine;
-template <> struct Combine<true> {
-    float inv;
-    int r;
-    __device__ __forceinline__ explicit Combine(uint64_t fin) : inv(1.0f / unpack<true>(fin).m), r(unpack<true>(fin).r) {}
-    __device__ __forceinline__ float operator()(uint64_t R, uint64_t Q) const
-    {
-        const Cell<true> a = unpack<true>(R), q = unpack<true>(Q);
-        return __builtin_amdgcn_ldexpf(a.m * (q.m * inv), sat_sub(sat_sub(r, a.r), q.r));
-    }
-};
-template <> struct Combine<false> {
-    double fin;
-    __device__ __forceinline__ explicit Combine(uint64_t f) : fin(unpack<false>(f).v) {}
-    __device__ __forceinline__ float operator()(uint64_t R, uint64_t Q) const
-    {
-        return __builtin_amdgcn_exp2f((float)((fin - unpack<false>(R).v) - unpack<false>(Q).v));
-    }
-};
 
 template <bool LOOK_FIRST>  // find the columns that can hold a non-zero E before reading the tables
 __global__ __launch_bounds__(64) void alignment_kernel(Params p, int seg_blocks)
@@ -2109,9 +1894,8 @@ __global__ __launch_bounds__(64) void alignment_kernel(Params p, int seg_blocks)
     float *Eb = p.E + (size_t)b * p.N * p.M;
     unsigned char *nzb = p.nz + (size_t)b * p.nrb * p.ncb;
     const ptrdiff_t band_off = (((ptrdiff_t)b * p.nbands + k) * (ptrdiff_t)p.nm_tab - table_base(p, k)) * kBlk * kBandRows;
-    const uint64_t *Rk = p.R + band_off, *Qk = p.Q + band_off;
-    const uint64_t fin = p.rfinal[b];
-    const bool scaled = p.hdr->scaled != 0;
+    const double *Rk = p.R + band_off, *Qk = p.Q + band_off;
+    const double Rfin = p.rfinal[b];
     float *my_ring = ring + lane * kAlignRingStride;
     // With a band constraint (or per-pair lengths) only macro-steps rg.lo .. rg.hi of the tables exist.
     // The blocks of the run that the sweeps did not cover are outside the window: flags cleared.
@@ -2125,10 +1909,7 @@ __global__ __launch_bounds__(64) void alignment_kernel(Params p, int seg_blocks)
     if constexpr (LOOK_FIRST) {
         if (rg.hi >= rg.lo) {
             int first, last;
-            if (scaled)
-                live_columns<true>(p, b, k, Nl, Ml, fin, lane, first, last);
-            else
-                live_columns<false>(p, b, k, Nl, Ml, fin, lane, first, last);
+            live_columns(p, b, k, Nl, Ml, Rfin, lane, first, last);
             first = __builtin_amdgcn_readfirstlane(first);  // the same in every lane: keep them scalar
             last = __builtin_amdgcn_readfirstlane(last);
             if (first <= last) {
@@ -2149,7 +1930,7 @@ __global__ __launch_bounds__(64) void alignment_kernel(Params p, int seg_blocks)
     const int g_end = min(min(cb1 + 2, p.nmacro), rg.hi + 1);  // macro-steps [g_first, g_end) hold every cell of the run
     if (g_first >= g_end) return;
 
-    auto load = [&](int g, uint64_t (&r)[kBlk], uint64_t (&q)[kBlk]) {
+    auto load = [&](int g, double (&r)[kBlk], double (&q)[kBlk]) {
         const size_t o = (size_t)g * kBlk * kBandRows + lane;
 #pragma unroll
         for (int u = 0; u < kBlk; ++u) {
@@ -2157,17 +1938,10 @@ __global__ __launch_bounds__(64) void alignment_kernel(Params p, int seg_blocks)
             q[u] = __builtin_nontemporal_load(&Qk[o + (size_t)u * kBandRows]);
         }
     };
-    const Combine<true> e_scaled(fin);
-    const Combine<false> e_log(fin);
-    auto process = [&](int g, const uint64_t (&r)[kBlk], const uint64_t (&q)[kBlk]) {
+    auto process = [&](int g, const double (&r)[kBlk], const double (&q)[kBlk]) {
         float *wr = my_ring + (g & 1) * kBlk;  // step s = 32g + u sits at ring slot s mod 64
-        if (scaled) {
 #pragma unroll
-            for (int u = 0; u < kBlk; ++u) wr[u] = e_scaled(r[u], q[u]);
-        } else {
-#pragma unroll
-            for (int u = 0; u < kBlk; ++u) wr[u] = e_log(r[u], q[u]);
-        }
+        for (int u = 0; u < kBlk; ++u) wr[u] = __builtin_amdgcn_exp2f((float)((Rfin - r[u]) - q[u]));
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         // complete now: (upper rows, block g-1) and (lower rows, block g-2)
         if (g - 1 >= cb0 && g - 1 < cb1) flush_E_block<kAlignRingCols, kAlignRingStride>(p, rg, ring, Eb, nzb, 0, g - 1, row0, lane);
@@ -2175,7 +1949,7 @@ __global__ __launch_bounds__(64) void alignment_kernel(Params p, int seg_blocks)
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     };
 
-    uint64_t ra[kBlk], qa[kBlk], rb[kBlk], qb[kBlk];
+    double ra[kBlk], qa[kBlk], rb[kBlk], qb[kBlk];
     int g = g_first;
     load(g, ra, qa);
     while (g < g_end) {
@@ -2218,15 +1992,14 @@ __global__ __launch_bounds__(64 * NW) void alignment_row_kernel(Params p)
     float *Eb = p.E + (size_t)b * p.N * p.M;
     unsigned char *nzb = p.nz + (size_t)b * p.nrb * p.ncb;
     const ptrdiff_t band_off = (((ptrdiff_t)b * p.nbands + k) * (ptrdiff_t)p.nm_tab - table_base(p, k)) * kBlk * kBandRows;
-    const uint64_t *Rk = p.R + band_off, *Qk = p.Q + band_off;
-    const uint64_t fin = p.rfinal[b];
-    const bool scaled = p.hdr->scaled != 0;
+    const double *Rk = p.R + band_off, *Qk = p.Q + band_off;
+    const double Rfin = p.rfinal[b];
     const SweepRange rg = sweep_range(p, row0, row0, pair_len(p.x_len, b, p.N), pair_len(p.y_len, b, p.M));
     // this block row's cells lie in macro-steps rb ... ncb + rb
     const int g_begin = max(rg.lo, rb), g_end = min(min(rg.hi, p.ncb + rb) + 1, min(p.nmacro, NM));
     const int half = lane >> 5, r = lane & 31;
     float *my_ring = ring + r * kStride + half;
-    auto load = [&](int g, uint64_t (&rr)[kBlk / 2], uint64_t (&qq)[kBlk / 2]) {
+    auto load = [&](int g, double (&rr)[kBlk / 2], double (&qq)[kBlk / 2]) {
         const size_t o = ((size_t)g * kBlk + half) * kBandRows + kBlk * rb + r;
 #pragma unroll
         for (int u = 0; u < kBlk / 2; ++u) {
@@ -2234,20 +2007,13 @@ __global__ __launch_bounds__(64 * NW) void alignment_row_kernel(Params p)
             qq[u] = __builtin_nontemporal_load(&Qk[o + (size_t)(2 * u) * kBandRows]);
         }
     };
-    const Combine<true> e_scaled(fin);
-    const Combine<false> e_log(fin);
-    auto process = [&](int g, const uint64_t (&rr)[kBlk / 2], const uint64_t (&qq)[kBlk / 2]) {
+    auto process = [&](int g, const double (&rr)[kBlk / 2], const double (&qq)[kBlk / 2]) {
         float *wr = my_ring + g * kBlk;  // step s = 32g + 2u + half sits at position s of the row
-        if (scaled) {
 #pragma unroll
-            for (int u = 0; u < kBlk / 2; ++u) wr[2 * u] = e_scaled(rr[u], qq[u]);
-        } else {
-#pragma unroll
-            for (int u = 0; u < kBlk / 2; ++u) wr[2 * u] = e_log(rr[u], qq[u]);
-        }
+        for (int u = 0; u < kBlk / 2; ++u) wr[2 * u] = __builtin_amdgcn_exp2f((float)((Rfin - rr[u]) - qq[u]));
     };
     {
-        uint64_t ra[kBlk / 2], qa[kBlk / 2], rc[kBlk / 2], qc[kBlk / 2];
+        double ra[kBlk / 2], qa[kBlk / 2], rc[kBlk / 2], qc[kBlk / 2];
         int g = g_begin + w;
         if (g < g_end) load(g, ra, qa);
         if (refused) {
@@ -2295,8 +2061,8 @@ __global__ __launch_bounds__(wg_threads(SLOTS, NPROD)) void forward_dp_kernel(Pa
 {
     __shared__ WgShared<SLOTS> sh;
     __shared__ unsigned ticket_s;
-    __shared__ uint64_t edge_out[SLOTS][kEdgeOut];
-    __shared__ uint64_t hand[kHandDoubles];
+    __shared__ double edge_out[SLOTS][kEdgeOut];
+    __shared__ double hand[kHandDoubles];
     forward_dp_body<KCH, SLOTS, NPROD>(p, value, sh, ticket_s, edge_out, hand);
 }
 
@@ -2305,8 +2071,8 @@ __global__ __launch_bounds__(wg_threads(SLOTS, NPROD)) void backward_dp_kernel(P
 {
     __shared__ WgShared<SLOTS> sh;
     __shared__ unsigned ticket_s;
-    __shared__ uint64_t edge_out[SLOTS][kEdgeOut];
-    __shared__ uint64_t hand[kHandDoubles];
+    __shared__ double edge_out[SLOTS][kEdgeOut];
+    __shared__ double hand[kHandDoubles];
     reverse_dp_body<KCH, SLOTS, NPROD, GRAD>(p, sh, ticket_s, edge_out, hand);
 }
 
@@ -2316,8 +2082,8 @@ __global__ __launch_bounds__(wg_threads(SLOTS, NPROD)) void both_sweeps_kernel(P
     static_assert(SLOTS == 1 || SLOTS == 2, "the shapes of small problems");
     __shared__ WgShared<SLOTS> sh;
     __shared__ unsigned ticket_s;
-    __shared__ uint64_t edge_out[SLOTS][kEdgeOut];
-    __shared__ uint64_t hand[kHandDoubles];
+    __shared__ double edge_out[SLOTS][kEdgeOut];
+    __shared__ double hand[kHandDoubles];
     if (blockIdx.x & 1)
         reverse_dp_body<KCH, SLOTS, NPROD>(p, sh, ticket_s, edge_out, hand);
     else

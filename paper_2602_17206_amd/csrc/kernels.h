@@ -24,7 +24,7 @@ __device__ __forceinline__ void fill_boundary_rows(const Params &p, unsigned lon
         for (size_t i = blk * blockDim.x + threadIdx.x; i < n; i += stride) rows[i] = kSentinel;
         return;
     }
-    const unsigned long long big = kBigBits;
+    const unsigned long long big = (unsigned long long)__double_as_longlong(kBig);
     for (size_t i = blk * blockDim.x + threadIdx.x; i < n; i += stride) {
         const int j = (int)(i % (size_t)p.M);
         const int k = (int)((i / (size_t)p.M) % (size_t)p.nbands);
@@ -70,46 +70,8 @@ __device__ __forceinline__ void split_scale(float mx, float &sc, float &inv)
     inv = ldexpf(1.0f, ex - 14);
 }
 
-// The largest norms a workgroup of 256 threads has seen, into its entry of Params::cmax.
-__device__ __forceinline__ void store_cost_maximum(const Params &p, size_t blk, float xmax, float ymax)
-{
-    __shared__ float2 part[4];
-    xmax = wave_max_f32(xmax);
-    ymax = wave_max_f32(ymax);
-    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = make_float2(xmax, ymax);
-    __syncthreads();
-    if (threadIdx.x == 0)
-        p.cmax[blk] = make_float2(fmaxf(fmaxf(part[0].x, part[1].x), fmaxf(part[2].x, part[3].x)),
-                                  fmaxf(fmaxf(part[0].y, part[1].y), fmaxf(part[2].y, part[3].y)));
-}
-
 __global__ __launch_bounds__(256) void forward_prep_kernel(Params p, int64_t xrows, int64_t yrows)
 {
-    float xmax = 0.f, ymax = 0.f;
-    // (padding beyond a pair's own lengths does not count; a sequence shared by all pairs goes by the longest)
-    auto longest = [&](const int32_t *lens, int64_t stride, int full) {
-        int n = full;
-        if (lens != nullptr && stride == 0) {
-            n = 1;
-            for (int b = 0; b < p.B; ++b) n = max(n, min(lens[b], full));
-        }
-        return n;
-    };
-    const bool want_max = p.nslots > 0;
-    const int xl = longest(p.x_len, p.xn_stride, p.N), yl = longest(p.y_len, p.yn_stride, p.M);
-    auto note_norm = [&](bool isx, int64_t lr, float norm) {
-        const int32_t *lens = isx ? p.x_len : p.y_len;
-        if (lens != nullptr) {
-            const int full = isx ? p.N : p.M;
-            const int64_t b = lr / full;
-            const int n = (isx ? p.xn_stride : p.yn_stride) == 0 ? (isx ? xl : yl) : max(1, min(lens[b], full));
-            if (lr - b * full >= n) return;
-        }
-        if (isx)
-            xmax = fmaxf(xmax, norm);
-        else
-            ymax = fmaxf(ymax, norm);
-    };
     if (threadIdx.x == 0 && blockIdx.x == 0) stamp_header(p);
     fill_boundary_rows(p, p.brow, false, blockIdx.x, gridDim.x);
     if (p.two_sweep) fill_boundary_rows(p, p.brow_b, true, blockIdx.x, gridDim.x);  // the reverse sweep runs in the same call
@@ -153,7 +115,6 @@ __global__ __launch_bounds__(256) void forward_prep_kernel(Params p, int64_t xro
                 if (k0 == 0) {
                     (isx ? p.xn : p.yn)[lr] = acc;
                     (isx ? p.xis : p.yis)[lr] = ldexpf(1.0f, ex - 14);
-                    note_norm(isx, lr, acc);
                 }
                 typedef _Float16 half4 __attribute__((ext_vector_type(4)));
                 half4 h1, h2;
@@ -169,7 +130,6 @@ __global__ __launch_bounds__(256) void forward_prep_kernel(Params p, int64_t xro
             }
             cur = nxt;
         }
-        if (want_max) store_cost_maximum(p, blockIdx.x, xmax, ymax);
         return;
     }
     // One wavefront per row, lanes stride over the features.  Up to 256 features stay in registers
@@ -211,10 +171,7 @@ __global__ __launch_bounds__(256) void forward_prep_kernel(Params p, int64_t xro
             acc += __shfl_xor(acc, o);
             mx = fmaxf(mx, __shfl_xor(mx, o));
         }
-        if (lane == 0) {
-            (isx ? p.xn : p.yn)[lr] = acc;
-            note_norm(isx, lr, acc);
-        }
+        if (lane == 0) (isx ? p.xn : p.yn)[lr] = acc;
         if (p.Dp > 0) {
             // Split-half copy for the fp16 matrix cores: with a power-of-two scale s that brings the
             // row's largest magnitude into [2^13, 2^14), v*s = h1 + h2 + e with h1, h2 float16 and
@@ -244,7 +201,6 @@ __global__ __launch_bounds__(256) void forward_prep_kernel(Params p, int64_t xro
 #pragma unroll
         for (int c = 0; c < kRegs; ++c) cur[c] = nxt[c];
     }
-    if (want_max) store_cost_maximum(p, blockIdx.x, xmax, ymax);
 }
 
 // Does the workspace hold the forward of this descriptor?  Every field is read before any is
@@ -955,7 +911,6 @@ __global__ void export_R_kernel(Params p, double *__restrict__ dst)
     size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     const size_t stride = (size_t)gridDim.x * blockDim.x;
     const size_t band_elems = (size_t)p.nm_tab * kBlk * kBandRows;
-    const bool scaled = p.hdr->scaled != 0;
     for (; e < n; e += stride) {
         const int j = (int)(e % p.M);
         const size_t bi = e / p.M;
@@ -963,12 +918,9 @@ __global__ void export_R_kernel(Params p, double *__restrict__ dst)
         const int b = (int)(bi / p.N);
         const int k = i / kBandRows, t = i % kBandRows;
         const int sg = (j + t) / kBlk - table_base(p, k);  // macro-step within the band's table
-        double v = __builtin_inf();
-        if (sg >= 0 && sg < p.nm_tab) {
-            const uint64_t bits = p.R[((size_t)b * p.nbands + k) * band_elems + ((size_t)sg * kBlk + (j + t) % kBlk) * kBandRows + t];
-            v = scaled ? cell_log2(unpack<true>(bits)) / (double)p.c2f : cell_log2(unpack<false>(bits)) * p.inv_c2d;
-        }
-        dst[e] = v;
+        dst[e] = (sg < 0 || sg >= p.nm_tab) ? __builtin_inf()
+                                            : p.R[((size_t)b * p.nbands + k) * band_elems +
+                                                  ((size_t)sg * kBlk + (j + t) % kBlk) * kBandRows + t] * p.inv_c2d;
     }
 }
 

@@ -5,7 +5,6 @@
 // anti-diagonal (Sec. 4.1: cells of an anti-diagonal are independent).  Steps are grouped in
 // macro-steps of 32 because the cost arrives in 32x32 blocks.
 #pragma once
-#include <hip/hip_runtime.h>
 #include <stddef.h>
 #include <stdint.h>
 
@@ -15,12 +14,7 @@ constexpr int kBandRows = 64;    // rows per band == lanes per wavefront
 constexpr int kBlk = 32;         // edge of a cost block (one 32x32 MFMA tile)
 constexpr uint64_t kSentinel = 0xFFFFFFFFFFFFFFFFull;  // "not written yet" in boundary rows
 constexpr uint32_t kMagic = 0x53445457u;               // 'SDTW'
-// Stands for "no alignment ends here" (+inf) in the DP tables and boundary rows, in both representations of
-// a table entry (Cell in device_core.h): about 1e300 as a float64, and mantissa 0 at a scale beyond every real
-// one as a (mantissa, scale) pair.
-constexpr uint64_t kBigBits = 0x7E37E43C00000000ull;
-constexpr double kBig = __builtin_bit_cast(double, kBigBits);
-constexpr int kMaxSlots = 1024;                        // workgroups that make the norms, at most, where the sweeps may use scaled entries
+constexpr double kBig = 1e300;                         // stands for +inf in the DP tables and boundary rows
 constexpr int32_t kNoWindow = 0x3FFFFFFF;              // Params::window when there is no band constraint
 constexpr int kGuardBytes = 512;  // slack before/after regions that are read with clamped indices
 
@@ -40,8 +34,7 @@ struct Header {
     uint32_t pool_count;   // compact E: 32x32 blocks handed out so far (may run past the capacity)
     int32_t pool_overflow; // compact E: a block did not fit; the backward call redoes the gradients the slow way
     int32_t pieces;        // float16 pieces per operand element the forward was run with (Params::pieces)
-    int32_t scaled;        // the tables hold (mantissa, scale) pairs, not float64 logarithms (Cell in device_core.h)
-    uint32_t pad[42];
+    uint32_t pad[43];
 };
 static_assert(sizeof(Header) == 256, "header is 256 bytes");
 
@@ -59,7 +52,7 @@ struct Layout {
     int32_t two_sweep;           // 1: the forward call also runs the reverse sweep and stores its table Q
     int32_t compact_E;           // 1: E is kept as a pool of its non-zero 32x32 blocks, not as a dense tensor (see make_layout)
     int64_t pool_blocks;         // capacity of that pool
-    size_t off_hdr, off_rfinal, off_cmax, off_xn, off_yn, off_xis, off_yis, off_xh, off_yh, off_brow, off_brow_b, off_R,
+    size_t off_hdr, off_rfinal, off_xn, off_yn, off_xis, off_yis, off_xh, off_yh, off_brow, off_brow_b, off_R,
         off_Q, off_ckpt, off_cost, off_E, off_nz, off_idx, off_pool, off_rsum, off_csum, off_dyhi, off_pexp, off_self, total;
 };
 
@@ -104,7 +97,6 @@ inline Layout make_layout(int32_t B, int32_t N, int32_t M, int32_t D, int32_t mo
     size_t o = 0;
     L.off_hdr = o;      o += sizeof(Header);
     L.off_rfinal = o;   o = align_up(o + (size_t)B * sizeof(double), 256);
-    L.off_cmax = o;     o = align_up(o + (size_t)kMaxSlots * 2 * sizeof(float), 256);
     L.off_xn = o;       o = align_up(o + (size_t)L.xn_count * sizeof(float), 256);
     L.off_yn = o;       o = align_up(o + (size_t)L.yn_count * sizeof(float), 256);
     L.Dp = D <= 16 ? 16 : (D <= 32 ? 32 : (D <= 64 ? 64 : (D <= kMaxSplitD ? 128 : 0)));
@@ -182,9 +174,6 @@ struct Params {
     float gamma;
     double c2d;             // log2(e)/gamma: paper units -> table units
     double inv_c2d;         // gamma*ln(2): table units -> paper units
-    float c2f;              // c2d in float32: the scale of the costs in the (mantissa, scale) representation
-    int32_t nslots;         // entries of cmax; 0: not wanted, logarithmic tables
-    float2 *cmax;           // per workgroup of the kernel that makes the norms: largest ||x_i||^2 and ||y_j||^2 it saw
     int64_t x_stride, y_stride;    // batch strides of x, y (elements)
     int64_t xn_stride, yn_stride;  // batch strides of the norm vectors (0 when shared)
     int32_t vec_xy;                // 1: D%8==0 and x,y 16-byte aligned -> float4 operand loads
@@ -195,7 +184,7 @@ struct Params {
     const int32_t *x_len, *y_len;  // ragged batches: per-pair lengths (device), or nullptr
     int32_t window;                // only cells with |i-j| <= window belong to the grid (kNoWindow: all do)
     Header *hdr;
-    uint64_t *rfinal;              // per pair: the table entry R[N,M]
+    double *rfinal;
     float *xn, *yn;
     int32_t Dp;                    // row length (halves) of the split operand copies, 0 if absent
     int32_t pieces;                // 2: x, y are float32, each element is two float16 pieces (three matrix-core products);
@@ -206,9 +195,9 @@ struct Params {
     int64_t xh_stride, yh_stride;  // batch strides of the split copies (0 when shared)
     unsigned long long *brow;      // boundary rows of the forward sweep
     unsigned long long *brow_b;    // boundary rows of the backward sweep (rows of its own whenever a backward can follow)
-    uint64_t *R;                   // tables: 64-bit entries, see Cell
-    uint64_t *Q;                   // two_sweep: table of the reverse sweep (soft-minimum part), ordered like R
-    uint64_t *ckpt;                // large problems: forward lane state per macro-step instead of R
+    double *R;
+    double *Q;                     // two_sweep: table of the reverse sweep (soft-minimum part), ordered like R
+    double *ckpt;                  // large problems: forward lane state per macro-step instead of R
     int32_t two_sweep;
     float *cost;
     float *E;                      // alignment matrix, dense: in the workspace, or the caller's E_out where the workspace has none

@@ -135,10 +135,7 @@ Params make_params(const sdtw_desc *d, const Layout &L, const float *x, const fl
     p.spin_limit = g_spin_limit;
     p.x = x; p.y = y;
     p.hdr = reinterpret_cast<Header *>(base + L.off_hdr);
-    p.c2f = (float)p.c2d;
-    p.rfinal = reinterpret_cast<uint64_t *>(base + L.off_rfinal);
-    p.cmax = reinterpret_cast<float2 *>(base + L.off_cmax);
-    p.nslots = 0;  // (set by the forward call)
+    p.rfinal = reinterpret_cast<double *>(base + L.off_rfinal);
     p.xn = reinterpret_cast<float *>(base + L.off_xn);
     p.yn = reinterpret_cast<float *>(base + L.off_yn);
     p.Dp = L.Dp;
@@ -150,10 +147,10 @@ Params make_params(const sdtw_desc *d, const Layout &L, const float *x, const fl
     p.yh_stride = d->y_batch_stride == 0 ? 0 : (int64_t)d->M * L.Dp * 2;
     p.brow = reinterpret_cast<unsigned long long *>(base + L.off_brow);
     p.brow_b = reinterpret_cast<unsigned long long *>(base + L.off_brow_b);
-    p.R = reinterpret_cast<uint64_t *>(base + L.off_R);
-    p.Q = reinterpret_cast<uint64_t *>(base + L.off_Q);
+    p.R = reinterpret_cast<double *>(base + L.off_R);
+    p.Q = reinterpret_cast<double *>(base + L.off_Q);
     p.two_sweep = L.two_sweep;
-    p.ckpt = reinterpret_cast<uint64_t *>(base + L.off_ckpt);
+    p.ckpt = reinterpret_cast<double *>(base + L.off_ckpt);
     p.cost = reinterpret_cast<float *>(base + L.off_cost);
     p.E = L.compact_E ? nullptr : reinterpret_cast<float *>(base + L.off_E);  // (compact: the caller's E_out, if any)
     p.nz = reinterpret_cast<unsigned char *>(base + L.off_nz);
@@ -214,9 +211,8 @@ void launch_dp_kch(const sdtw_desc *d, const Layout &L, const Params &p, float *
                 const unsigned tasks = (unsigned)d->B * (unsigned)L.nbands;
                 // about four workgroups per compute unit: the wavefronts share SIMDs anyway, and one
                 // producer per band (two wavefronts per workgroup instead of three) leaves the consumers
-                // more of them.  Not at D > 64: a single producer is what the (scaled) chain waits for then
-                // (N = M = 1024, B = 32, D = 128: 416 us, 337 us with two).
-                if (L.two_sweep && KCH > 0 && KCH < 8 && 2 * tasks > 900)
+                // more of them (3 % at N = M = 1024, B = 32)
+                if (L.two_sweep && KCH > 0 && 2 * tasks > 900)
                     both_sweeps_kernel<KCH, 1, 1><<<2 * tasks, wg_threads(1, 1), 0, st>>>(p, value);
                 else if (L.two_sweep)
                     both_sweeps_kernel<KCH, 1, NP><<<2 * tasks, wg_threads(1, NP), 0, st>>>(p, value);
@@ -280,9 +276,7 @@ int forward_impl(const sdtw_desc *d, const float *x, const float *y, float *valu
 {
     (void)hipGetLastError();  // what an earlier, unrelated call left behind is not this call's error
     const Layout L = layout_of(d);
-    Params p = make_params(d, L, x, y, ws, x_len, y_len, pieces);
-    // Scaled table entries where the shape may use them (may_scale); the norms' maxima are wanted then.
-    const bool scaled = small_problem(d);
+    const Params p = make_params(d, L, x, y, ws, x_len, y_len, pieces);
     // Unfused mode, small problems: the start of the call is folded into the cost-tensor kernel (one
     // launch instead of two).  Not with a band constraint or length vectors (tiles outside them are
     // skipped), not without 16-byte rows, and only where the tiles are few (fewer than 512 of 128 x 128):
@@ -293,17 +287,13 @@ int forward_impl(const sdtw_desc *d, const float *x, const float *y, float *valu
                         tiles128 < 512;
     if (!folded) {
         ProfScope ps("forward_prep", st);
-        unsigned grid = prep_grid(p, L.xn_count + L.yn_count);
-        if (scaled) p.nslots = (int)(grid = std::min(grid, (unsigned)kMaxSlots));  // every sweep workgroup reads them all:
-        // at B = 64, L = 512, D = 32 a step takes 180.3 us with at most 1024, 185.7 us with 2048
-        forward_prep_kernel<<<grid, 256, 0, st>>>(p, L.xn_count, L.yn_count);
+        forward_prep_kernel<<<prep_grid(p, L.xn_count + L.yn_count), 256, 0, st>>>(p, L.xn_count, L.yn_count);
     }
     if (d->mode == SDTW_UNFUSED) {
         ProfScope ps("cost_tensor", st);
         // 128 x 128 tiles, or 128 x 64 when those would leave most of the chip idle
         const bool narrow = tiles128 < 512;
         dim3 gh(narrow ? (d->M + 63) / 64 : (d->M + 127) / 128, (d->N + 127) / 128, d->B);
-        if (folded && scaled) p.nslots = (int)(gh.x * gh.y * gh.z);  // fewer than kMaxSlots: at most twice tiles128 < 512
         auto launch = [&](auto kg) {
             constexpr int KG = decltype(kg)::value;
             if (folded)
