@@ -87,9 +87,12 @@ int64_t busy_bands(const sdtw_desc *d)
 }
 
 // Problems of up to about 1536 busy band tasks cannot fill the chip: they run one band per workgroup
-// (measured: 19 % faster than the 4-band workgroups at 1536 tasks, equal at 2048, 40 % slower at 4096).
-// (Under a band constraint the estimate of the busy bands is coarse; measured at B = 32, N = M = 8192
-// and B = 128, N = M = 2048 the one-band workgroups win up to about 640.)
+// (forward + backward at N = M = 1024, D = 128, one-band / 4-band workgroups: 1536 tasks fused 0.88 / 1.12 ms,
+// unfused 0.98 / 1.05; 1792 tasks 1.03 / 1.11, 1.13 / 1.09; 2048 tasks 1.19 / 1.16, 1.31 / 1.18; 4096 tasks 2.42 / 1.87,
+// 2.63 / 2.03.  Narrower features cross over later in fused mode: D = 50, 2048 tasks 0.77 / 0.87.)
+// Under a band constraint the estimate of the busy bands is coarse, and the line is on the safe side: at B = 32,
+// N = M = 8192 a bandwidth of 1024 (512 by the estimate) takes 4.3 / 7.5 ms, 2048 (896) 6.7 / 7.6; at B = 128,
+// N = M = 2048 bandwidths of 64 and 256 (512 and 768) take 1.33 / 2.11 and 1.85 / 2.13 ms.
 bool small_problem(const sdtw_desc *d)
 {
     if (g_force_slots) return g_force_slots != 4;
@@ -193,9 +196,9 @@ void launch_dp_kch(const sdtw_desc *d, const Layout &L, const Params &p, float *
         // Pairs of consecutive bands share a workgroup (the hand-over between them stays in LDS)
         // when there are at least two bands and the producers are light: in the chained shape the
         // producers of a band share one SIMD, which the D = 128 matrix-core producers fill
-        // (measured at N = M = 256: 57 us chained against 54 us, but 50 us against 53 us unfused).
+        // (forward + backward at N = M = 256, B = 32, D = 128, chained / unchained: 94.9 / 86.0 us fused, 87.6 / 88.9 unfused).
         // It also wants a compute unit per workgroup: two chained workgroups on one compute unit put
-        // two consumers on one SIMD (measured at N = M = 1024, B = 32: 5 % slower than unchained).
+        // two consumers on one SIMD (N = M = 1024, B = 32: 438 / 404 us unfused, 381 / 380 fused).
         const bool light = d->mode == SDTW_UNFUSED || d->D <= 64;
         const bool roomy = (int64_t)d->B * ((busy_bands(d) + 1) / 2) * (L.two_sweep ? 2 : 1) <= 256;
         // (under a band constraint the chain of band hops is all there is: chaining pays there too, 3-4 %)
@@ -211,7 +214,9 @@ void launch_dp_kch(const sdtw_desc *d, const Layout &L, const Params &p, float *
                 const unsigned tasks = (unsigned)d->B * (unsigned)L.nbands;
                 // about four workgroups per compute unit: the wavefronts share SIMDs anyway, and one
                 // producer per band (two wavefronts per workgroup instead of three) leaves the consumers
-                // more of them (3 % at N = M = 1024, B = 32)
+                // more of them.  Forward + backward with one / two producers: N = M = 1024, B = 32, D = 39
+                // 307 / 338 us, but D = 128 368 / 349 us (there the one is what the chain waits for);
+                // N = M = 512, B = 64, D = 32 189 / 186 us
                 if (L.two_sweep && KCH > 0 && 2 * tasks > 900)
                     both_sweeps_kernel<KCH, 1, 1><<<2 * tasks, wg_threads(1, 1), 0, st>>>(p, value);
                 else if (L.two_sweep)
